@@ -34,7 +34,7 @@ HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize
 def build(verbose: bool = False, sanitize_host: bool = False) -> str:
     cmd = ["/opt/rocm/bin/hipcc", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
            "-ffp-contract=on",
-           "-shared", "-Wall", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-shared", "-Wall", "-parallel-jobs=4", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            "-o", LIB + ".tmp"] + (HOST_SANITIZE if sanitize_host else []) + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:

@@ -508,6 +508,7 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
   c->launch.step_w = std::min(step_width_for(p->nx, p->ny, p->dtype), pm::TILE);
   c->launch.step_tiles_x = (p->nx + c->launch.step_w - 1) / c->launch.step_w;
   c->launch.step_ntiles = c->launch.step_tiles_x * p->ny;
+  c->launch.near = lay.pop_bytes <= pm::NEAR_BYTES;
   c->red = (double*)((char*)dev_ws + lay.off_red);
   hipError_t e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
@@ -773,6 +774,7 @@ struct pm_sweep {
   int sched_live;       // cases live when the schedule was built
   int tile_w, tile_h;   // sweep tile: tile_w columns by tile_h rows (pm_sweep_set_tile)
   bool any_sr;          // some case rounds stochastically (PM_ROUND_STOCHASTIC)
+  bool near;            // the scheduled cases' populations are at most NEAR_BYTES together
   void* d_cases;        // SweepCase<T>[ncases]
   int2* d_sched;        // schedule entries (case, tile)
   int* d_live;          // 1 while the case still runs
@@ -865,6 +867,9 @@ void build_schedule(pm_sweep* s) {
   for (int i = 0; i < n; ++i)
     if (live(i)) ids.push_back(i);
   s->sched_live = (int)ids.size();
+  size_t bytes = 0;
+  for (int i : ids) bytes += s->ctx[i]->lay.pop_bytes;
+  s->near = bytes <= pm::NEAR_BYTES;
   if (s->order == PM_ORDER_LARGEST)
     std::stable_sort(ids.begin(), ids.end(), [&](int a, int b) { return s->ntiles[a] > s->ntiles[b]; });
   s->h_sched.clear();
@@ -889,10 +894,10 @@ hipError_t sweep_enqueue_chunk(pm_sweep* s, hipStream_t st, int64_t chunk, int p
     const int par = (int)((parity0 + t) & 1);
     if (s->dtype == PM_FP64)
       e = pm::launch_step_multi<double>((const pm::SweepCase<double>*)s->d_cases, s->d_sched, s->d_live,
-                                        s->nsched, par, s->tile_w, s->tile_h, s->any_sr, st);
+                                        s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->near, st);
     else
       e = pm::launch_step_multi<float>((const pm::SweepCase<float>*)s->d_cases, s->d_sched, s->d_live,
-                                       s->nsched, par, s->tile_w, s->tile_h, s->any_sr, st);
+                                       s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->near, st);
   }
   if (e != hipSuccess) return e;
   const int par_end = (int)((parity0 + chunk) & 1);
@@ -1185,10 +1190,10 @@ int pm_sweep_step(pm_sweep* s, int64_t k) {
     const int par = (int)((s->gsteps + t) & 1);
     if (s->dtype == PM_FP64)
       e = pm::launch_step_multi<double>((const pm::SweepCase<double>*)s->d_cases, s->d_sched, s->d_live,
-                                        s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->stream);
+                                        s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->near, s->stream);
     else
       e = pm::launch_step_multi<float>((const pm::SweepCase<float>*)s->d_cases, s->d_sched, s->d_live,
-                                       s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->stream);
+                                       s->nsched, par, s->tile_w, s->tile_h, s->any_sr, s->near, s->stream);
   }
   if (e != hipSuccess) return sweep_fail(s, PM_EDEVICE, "pm_sweep_step: %s", hipGetErrorString(e));
   // live cases advance together; the per-case counters follow on the device

@@ -18,12 +18,17 @@ constexpr int OPP[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
 constexpr int EXv[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 constexpr int EYv[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
-// Workgroup b handles row tile b in row-major order.  Dispatch deals
-// consecutive workgroups round-robin to the 8 XCDs, so at any moment all XCDs
-// stream through one narrow band of rows, within few DRAM pages.  (Giving
-// each XCD its own contiguous band of rows, or groups of 2-64 consecutive
-// tiles, measured no faster.)
-__device__ __forceinline__ int tile_of_block(int b, int) { return b; }
+// Workgroups are dealt to the 8 XCDs in turn (workgroup b runs on XCD b mod 8).
+// band_of_block gives each XCD one contiguous band of the G tiles instead, so
+// that what a tile shares with its neighbours (halo rows, cache lines that its
+// edges split) stays within one XCD's L2, and an XCD meets the same rows again
+// in the next launch.  Used while the state stays in the caches (see NEAR_BYTES);
+// a state that streams from HBM keeps the launch order, where all XCDs read one
+// narrow band of rows, within few DRAM pages.
+__device__ __forceinline__ int band_of_block(int b, int G) {
+  const int x = b & 7, per = G >> 3, rem = G & 7;
+  return x * per + min(x, rem) + (b >> 3);
+}
 
 // Arithmetic helpers.  FP32 uses the hardware approximations directly
 // (v_rcp_f32, v_exp_f32, v_log_f32, v_sqrt_f32, about 1 ulp): the FP32 path is
@@ -168,20 +173,20 @@ __device__ __forceinline__ unsigned in_off(const KParams<T, S>& p, int q, int i,
   return (unsigned)(q * p.qs + (1 + dy) * p.rs + (i + dx));
 }
 
-template <typename T, typename S>
+template <typename T, bool NT = true, typename S>
 __device__ __forceinline__ void load_interior_odd(const KParams<T, S>& p, const RowBase<S>& b, int i,
                                                   T df[9], T dg[5]) {
-  df[0] = ldg<T, true>(b.f + in_off(p, 0, i, 0, 0));
+  df[0] = ldg<T, NT>(b.f + in_off(p, 0, i, 0, 0));
 #pragma unroll
   for (int q = 1; q < 9; ++q) {
     const S* a = b.f + in_off(p, OPP[q], i, -EXv[q], -EYv[q]);
-    df[q] = EXv[q] == 0 ? ldg<T, true>(a) : ldg<T, false>(a);
+    df[q] = EXv[q] == 0 ? ldg<T, NT>(a) : ldg<T, false>(a);
   }
-  dg[0] = ldg<T, true>(b.g + in_off(p, 0, i, 0, 0));
+  dg[0] = ldg<T, NT>(b.g + in_off(p, 0, i, 0, 0));
 #pragma unroll
   for (int q = 1; q < 5; ++q) {
     const S* a = b.g + in_off(p, OPP[q], i, -EXv[q], -EYv[q]);
-    dg[q] = EXv[q] == 0 ? ldg<T, true>(a) : ldg<T, false>(a);
+    dg[q] = EXv[q] == 0 ? ldg<T, NT>(a) : ldg<T, false>(a);
   }
 }
 
@@ -206,14 +211,14 @@ __device__ __forceinline__ void store_interior_odd(const KParams<T, S>& p, const
 
 // Pre-collision populations of node (i, j) for a state of the given parity,
 // before the odd step's thermal wall conditions (pull_walls).
-template <typename T, bool ODD, typename S>
+template <typename T, bool ODD, bool NT = true, typename S>
 __device__ __forceinline__ void load_node_raw(const KParams<T, S>& p, int i, int j, T df[9], T dg[5]) {
   const int64_t o = pop_off(p, i, j);
   if (!ODD) {
 #pragma unroll
-    for (int q = 0; q < 9; ++q) df[q] = ldg<T, true>(p.f + q * p.qs + o);
+    for (int q = 0; q < 9; ++q) df[q] = ldg<T, NT>(p.f + q * p.qs + o);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) dg[q] = ldg<T, true>(p.g + q * p.qs + o);
+    for (int q = 0; q < 5; ++q) dg[q] = ldg<T, NT>(p.g + q * p.qs + o);
     return;
   }
   // Odd step: the pull of direction q into (i, j) reads population OPP[q] of
@@ -240,7 +245,7 @@ __device__ __forceinline__ void load_node_raw(const KParams<T, S>& p, int i, int
     const bool in = (EXv[d] > 0 ? in_im : (EXv[d] < 0 ? in_ip : true)) &
                     (EYv[d] > 0 ? in_jm : (EYv[d] < 0 ? in_jp : true));
     const int64_t idx = in ? OPP[d] * p.qs + rs + si : d * p.qs + o;
-    const T v = EXv[d] == 0 ? ldg<T, true>(base + idx) : ldg<T, false>(base + idx);
+    const T v = EXv[d] == 0 ? ldg<T, NT>(base + idx) : ldg<T, false>(base + idx);
     if (q < 9) df[q] = v;
     else dg[q - 9] = v;
   }
@@ -257,9 +262,9 @@ __device__ __forceinline__ void pull_walls(const KParams<T, S>& p, int i, T dg[5
 }
 
 // Pre-collision populations of node (i, j) for a state of the given parity.
-template <typename T, bool ODD, typename S>
+template <typename T, bool ODD, bool NT = true, typename S>
 __device__ __forceinline__ void load_node(const KParams<T, S>& p, int i, int j, T df[9], T dg[5]) {
-  load_node_raw<T, ODD>(p, i, j, df, dg);
+  load_node_raw<T, ODD, NT>(p, i, j, df, dg);
   if (ODD) pull_walls(p, i, dg);
 }
 
@@ -396,14 +401,13 @@ struct Macro {
 };
 
 // Steps 2-6 of the update for one node (shifted populations in registers):
-// moments, buoyancy, provisional velocity, viscosity, porous velocity.
+// moments, buoyancy, provisional velocity, viscosity, porous velocity.  ldk:
+// the node's log10(Da) (LOGDA), loaded by the caller with the populations.
 template <typename T, bool POW, bool LOGDA, typename S>
-__device__ __forceinline__ void node_macros(const KParams<T, S>& p, int k, const T df[9],
+__device__ __forceinline__ void node_macros(const KParams<T, S>& p, T ldk, const T df[9],
                                             const T dg[5], T& drho, T& rho, T& jx, T& jy,
                                             T& dT, T& Gx, T& Gy, T& nu, T& ux, T& uy, T& invK,
                                             T& invsK, T& m1, T& m7, T& m8) {
-  // read first, so that the load is in flight with the node's populations
-  const T ldk = LOGDA ? (T)p.logda[k] : T(0);
   drho = (df[0] + ((df[1] + df[2]) + (df[3] + df[4]))) + ((df[5] + df[6]) + (df[7] + df[8]));
   rho = T(1) + drho;
   jx = ((df[1] - df[3]) + (df[5] - df[6])) - (df[7] - df[8]);
@@ -510,14 +514,21 @@ __device__ __forceinline__ float sr_add(float a, float b, float us) {
   else return dither_add(a, b, us);
 }
 
+// log10(Da) of node k (0 without a log-Da plane): loaded ahead of the node's
+// populations, so that it is in flight with them.
+template <bool LOGDA, typename T, typename S>
+__device__ __forceinline__ T load_logda(const KParams<T, S>& p, int k) {
+  return LOGDA ? p.logda[k] : T(0);
+}
+
 // The full local update: Steps 2-9 on shifted populations, in place.
 // With SR and half storage, *rw receives the node's random word for the
 // stores' stochastic conversion (the caller passes rw then).
 template <typename T, bool POW, bool LOGDA, bool SR = false, typename S>
-__device__ __forceinline__ void collide(const KParams<T, S>& p, int k, T df[9], T dg[5],
+__device__ __forceinline__ void collide(const KParams<T, S>& p, int k, T ldk, T df[9], T dg[5],
                                         unsigned* rw = nullptr) {
   T drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK, invsK, m1, m7, m8;
-  node_macros<T, POW, LOGDA>(p, k, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
+  node_macros<T, POW, LOGDA>(p, ldk, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
                              invsK, m1, m7, m8);
   // Step 7: force per unit mass (Darcy + Forchheimer drag, eps G)
   const T um = fsqrt<T>(ux * ux + uy * uy);
@@ -624,7 +635,7 @@ __device__ __forceinline__ void collide(const KParams<T, S>& p, int k, T df[9], 
 // scatter into the state d (d == p: the in-place AA update; d != p: the same
 // update written to another buffer, which then holds the complete next
 // state because every slot is written exactly once per step).
-template <typename T, bool ODD, bool POW, bool LOGDA, bool SR = false, typename S>
+template <typename T, bool ODD, bool POW, bool LOGDA, bool SR, bool NEAR, typename S>
 __device__ __forceinline__ void step_tile(const KParams<T, S>& p, const KParams<T, S>& d, int i0, int j, int lx) {
   const int i = i0 + lx;
   T df[9], dg[5];
@@ -637,15 +648,17 @@ __device__ __forceinline__ void step_tile(const KParams<T, S>& p, const KParams<
     const int w0 = i0 + (__builtin_amdgcn_readfirstlane(lx) & ~63);
     const bool interior = w0 >= 1 && w0 + 63 <= p.nx - 2 && j >= 1 && j <= p.ny - 2;
     if (interior) {
-      load_interior_odd<T>(p, row_base(p, j), i, df, dg);
-      collide<T, POW, LOGDA, SR>(p, j * p.nx + i, df, dg, &rw);
+      const T ldk = load_logda<LOGDA>(p, j * p.nx + i);
+      load_interior_odd<T, !NEAR>(p, row_base(p, j), i, df, dg);
+      collide<T, POW, LOGDA, SR>(p, j * p.nx + i, ldk, df, dg, &rw);
       store_interior_odd<T, HSR>(d, row_base(d, j), i, df, dg, rw);
       return;
     }
   }
   if (i >= p.nx) return;
-  load_node<T, ODD>(p, i, j, df, dg);
-  collide<T, POW, LOGDA, SR>(p, j * p.nx + i, df, dg, &rw);
+  const T ldk = load_logda<LOGDA>(p, j * p.nx + i);
+  load_node<T, ODD, !NEAR>(p, i, j, df, dg);
+  collide<T, POW, LOGDA, SR>(p, j * p.nx + i, ldk, df, dg, &rw);
   store_node<T, ODD, HSR>(d, i, j, df, dg, rw);
 }
 

@@ -89,7 +89,13 @@ struct Launch {
   int step_w;        // row-segment width of the step kernels' workgroups (64, 128 or 256)
   int step_tiles_x;  // ceil(nx / step_w)
   int step_ntiles;   // step_tiles_x * ny
+  bool near;         // the population region is at most NEAR_BYTES
 };
+
+// A state (all populations) of at most this many bytes stays in the 256 MB
+// last-level cache from step to step: the step kernels then take XCD bands and
+// cached loads (measured on both sides at k_step).
+constexpr size_t NEAR_BYTES = size_t(256) << 20;
 
 #ifndef PM_TILE
 #define PM_TILE 256
@@ -143,13 +149,14 @@ hipError_t launch_set_logda(const KParams<T, S>& p, const Launch& L, T* dst, con
                             int in_fp64);
 // Sweep tiles are tw columns by th rows: tw in {64, 128, 256}, th in {1, 2, 4},
 // tw * th <= TILE threads (a wave then lies within one grid row).  any_sr:
-// some case of the sweep rounds stochastically.
+// some case of the sweep rounds stochastically.  near: the scheduled cases'
+// states are at most NEAR_BYTES together.
 inline bool sweep_tile_ok(int tw, int th) {
   return (tw == 64 || tw == 128 || tw == 256) && (th == 1 || th == 2 || th == 4) && tw * th <= TILE;
 }
 template <typename T>
 hipError_t launch_step_multi(const SweepCase<T>* cases, const int2* sched, const int* live,
-                             int nsched, int parity, int tw, int th, bool any_sr, hipStream_t s);
+                             int nsched, int parity, int tw, int th, bool any_sr, bool near, hipStream_t s);
 template <typename T>
 hipError_t launch_resid_multi(const SweepCase<T>* cases, int ncases, const int2* sched, int* live,
                               int nsched, int parity, int tw, int th, double* partial, SweepStatus* st,

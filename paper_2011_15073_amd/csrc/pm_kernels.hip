@@ -22,7 +22,8 @@
 // contiguous block per grid row; one workgroup covers a row segment of 64,
 // 128 or 256 nodes (chosen by the host from the grid size and dtype), one
 // lane per node, so every load and store of a wave is a contiguous 256 B
-// (FP32) run; workgroups run in row-major tile order.  The
+// (FP32) run; workgroups run in row-major tile order (in XCD bands, with
+// cached loads, while the state fits the last-level cache: NEAR).  The
 // streaming hint is used on every access that is not shifted along x (those
 // lines are touched exactly once per step); the x-shifted accesses of the odd
 // step straddle lines that the neighbouring wave also touches, so they keep
@@ -38,19 +39,26 @@ namespace {
 using namespace pm::dev;
 
 // One workgroup per row segment of blockDim.x nodes (64, 128 or 256).
-template <typename T, bool ODD, bool POW, bool LOGDA, bool SR, typename S>
+// NEAR (the state fits the last-level cache, NEAR_BYTES): tiles in XCD bands
+// and cached loads; otherwise launch order and streaming loads.  us per step,
+// streaming / near: FP32 64^2 3.6 / 3.2, 256^2 4.5 / 3.8, 1024^2 21.4 / 20.3,
+// 2048^2 72.5 / 66.7 (3000^2 164 / 182); FP64 160^2 5.4 / 4.7, 512^2 13.0 /
+// 12.0, 1500^2 86.5 / 80.3 (2048^2 159 / 166); FP16 storage 256^2 4.0 / 3.5,
+// 1024^2 17.0 / 15.4, 3000^2 111 / 101 (4096^2 207 / 211).
+template <typename T, bool ODD, bool POW, bool LOGDA, bool SR, bool NEAR, typename S>
 __global__ __launch_bounds__(TILE) void k_step(KParams<T, S> p, int tiles_x, int ntiles) {
-  const int tile = tile_of_block(blockIdx.x, ntiles);
+  const int tile = NEAR ? band_of_block(blockIdx.x, ntiles) : blockIdx.x;
   const int j = tile / tiles_x;
-  step_tile<T, ODD, POW, LOGDA, SR>(p, p, (tile - j * tiles_x) * (int)blockDim.x, j, threadIdx.x);
+  step_tile<T, ODD, POW, LOGDA, SR, NEAR>(p, p, (tile - j * tiles_x) * (int)blockDim.x, j, threadIdx.x);
 }
 
 // The same step, read from state src and written to state dst (another
 // buffer of the same layout).
-template <typename T, bool ODD, bool POW, bool LOGDA, bool SR>
-__global__ __launch_bounds__(TILE) void k_step_oop(KParams<T> src, KParams<T> dst, int tiles_x) {
-  const int j = blockIdx.x / tiles_x;
-  step_tile<T, ODD, POW, LOGDA, SR>(src, dst, (blockIdx.x - j * tiles_x) * (int)blockDim.x, j, threadIdx.x);
+template <typename T, bool ODD, bool POW, bool LOGDA, bool SR, bool NEAR>
+__global__ __launch_bounds__(TILE) void k_step_oop(KParams<T> src, KParams<T> dst, int tiles_x, int ntiles) {
+  const int tile = NEAR ? band_of_block(blockIdx.x, ntiles) : blockIdx.x;
+  const int j = tile / tiles_x;
+  step_tile<T, ODD, POW, LOGDA, SR, NEAR>(src, dst, (tile - j * tiles_x) * (int)blockDim.x, j, threadIdx.x);
 }
 
 // ---- two time steps in one pass (FP32, cavity walls) ----
@@ -147,18 +155,24 @@ __global__ __launch_bounds__(TILE) void k_step2(KParams<float> src, KParams<floa
   // a + 1 are issued once row a has been collided, and are in flight while
   // rows a - 1 and a - 2 are finished (src is only read by this kernel).
   float nf[9] = {}, ng[5] = {};
-  if (col && y0 - 2 >= 0) load_node<float, false>(src, c, y0 - 2, nf, ng);
+  float nl = 0.0f;
+  if (col && y0 - 2 >= 0) {
+    nl = load_logda<LOGDA>(src, (y0 - 2) * src.nx + c);
+    load_node<float, false>(src, c, y0 - 2, nf, ng);
+  }
   for (int a = y0 - 2; a <= y_end + 1; ++a, s1 = s1 == 2 ? 0 : s1 + 1) {
     const int s1m = s1 == 0 ? 2 : s1 - 1, s1mm = s1m == 0 ? 2 : s1m - 1;
     // A: step k at row a
     {
       Still st{};
       if (col && a >= 0 && a < src.ny) {
-        collide<float, POW, LOGDA, SR>(src, a * src.nx + c, nf, ng);
+        collide<float, POW, LOGDA, SR>(src, a * src.nx + c, nl, nf, ng);
         put_row(ring1, s1, t, nf, ng, st);
       }
-      if (col && a + 1 >= 0 && a + 1 < src.ny && a + 1 <= y_end + 1)
+      if (col && a + 1 >= 0 && a + 1 < src.ny && a + 1 <= y_end + 1) {
+        nl = load_logda<LOGDA>(src, (a + 1) * src.nx + c);
         load_node<float, false>(src, c, a + 1, nf, ng);
+      }
       r1m = r10;
       r10 = r1p;
       r1p = st;
@@ -171,7 +185,7 @@ __global__ __launch_bounds__(TILE) void k_step2(KParams<float> src, KParams<floa
       if (b >= y0 - 1 && b >= 0 && b < src.ny && col && t >= 1 && t <= TILE - 2) {
         float df[9], dg[5];
         pull_pair(src, ring1, s1mm, s1m, s1, t, c, b, r1m, r10, r1p, df, dg);
-        collide<float, POW, LOGDA, SR>(src, b * src.nx + c, df, dg);
+        collide<float, POW, LOGDA, SR>(src, b * src.nx + c, load_logda<LOGDA>(src, b * src.nx + c), df, dg);
         put_row(ring2, s1m, t, df, dg, st);  // ring2 keeps row r in the slot ring1 gives row r
       }
       r2m = r20;
@@ -202,12 +216,15 @@ __global__ __launch_bounds__(TILE) void k_step2(KParams<float> src, KParams<floa
 // advanced here is bitwise identical to the same case advanced alone,
 // whatever the tile shape.  SR_ANY: some case rounds stochastically (FP32
 // only); without it the kernel carries no stochastic-rounding branch, which
-// would cost round-to-nearest sweeps registers and occupancy.
-template <typename T, bool ODD, bool SR_ANY>
+// would cost round-to-nearest sweeps registers and occupancy.  NEAR (as in
+// k_step): the live cases' states fit the last-level cache together.  The 27
+// FP32 cases (185 MB): 56.5 us per step near, 62.2 streaming; in FP64 (370 MB)
+// near would be 141 against 130.
+template <typename T, bool ODD, bool SR_ANY, bool NEAR>
 __global__ __launch_bounds__(TILE) void k_step_multi(const SweepCase<T>* __restrict__ cases,
                                                      const int2* __restrict__ sched,
                                                      const int* __restrict__ live, int tw, int th) {
-  const int2 e = sched[blockIdx.x];  // (case, tile within the case)
+  const int2 e = sched[NEAR ? band_of_block(blockIdx.x, gridDim.x) : blockIdx.x];  // (case, tile within the case)
   if (!live[e.x]) return;
   const SweepCase<T>& c = cases[e.x];
   const int ty = e.y / c.tiles_x;
@@ -216,13 +233,13 @@ __global__ __launch_bounds__(TILE) void k_step_multi(const SweepCase<T>* __restr
   const int i0 = (e.y - ty * c.tiles_x) * tw;
   if constexpr (SR_ANY && std::is_same<T, float>::value) {
     if (c.p.sr) {
-      if (c.pow) step_tile<T, ODD, true, false, true>(c.p, c.p, i0, j, lx);
-      else step_tile<T, ODD, false, false, true>(c.p, c.p, i0, j, lx);
+      if (c.pow) step_tile<T, ODD, true, false, true, NEAR>(c.p, c.p, i0, j, lx);
+      else step_tile<T, ODD, false, false, true, NEAR>(c.p, c.p, i0, j, lx);
       return;
     }
   }
-  if (c.pow) step_tile<T, ODD, true, false>(c.p, c.p, i0, j, lx);
-  else step_tile<T, ODD, false, false>(c.p, c.p, i0, j, lx);
+  if (c.pow) step_tile<T, ODD, true, false, false, NEAR>(c.p, c.p, i0, j, lx);
+  else step_tile<T, ODD, false, false, false, NEAR>(c.p, c.p, i0, j, lx);
 }
 
 // Rest state: df = 0, dg_q = w_q (T_init - T_ref).  (The padding of the
@@ -381,10 +398,11 @@ __global__ __launch_bounds__(TILE) void k_fields(KParams<T, S> p, O* U, O* V, O*
   if (i >= p.nx) return;
   for (int j = blockIdx.y; j < p.ny; j += gridDim.y) {
     T df[9], dg[5];
+    const int k = j * p.nx + i;
+    const T ldk = load_logda<LOGDA>(p, k);
     load_node<T, ODD>(p, i, j, df, dg);
     T drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK, invsK, m1, m7, m8;
-    const int k = j * p.nx + i;
-    node_macros<T, POW, LOGDA>(p, k, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
+    node_macros<T, POW, LOGDA>(p, ldk, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
                                invsK, m1, m7, m8);
     if (U) U[k] = (O)(ux * p.inv_U);
     if (V) V[k] = (O)(uy * p.inv_U);
@@ -534,8 +552,15 @@ template <typename T, typename S>
 hipError_t launch_step(const KParams<T, S>& p, const Launch& L, int parity, bool pow, bool logda) {
   if (!(L.step_w == 64 || L.step_w == 128 || L.step_w == 256) || L.step_w > TILE) return hipErrorInvalidValue;
   dim3 grid(L.step_ntiles), block(L.step_w);
-#define PM_STEP(ODD, POW, LOG, SR) \
-  hipLaunchKernelGGL((k_step<T, ODD, POW, LOG, SR, S>), grid, block, 0, L.stream, p, L.step_tiles_x, L.step_ntiles)
+#define PM_STEP(ODD, POW, LOG, SR)                                                                              \
+  do {                                                                                                         \
+    if (L.near)                                                                                                \
+      hipLaunchKernelGGL((k_step<T, ODD, POW, LOG, SR, true, S>), grid, block, 0, L.stream, p, L.step_tiles_x,  \
+                         L.step_ntiles);                                                                       \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_step<T, ODD, POW, LOG, SR, false, S>), grid, block, 0, L.stream, p, L.step_tiles_x, \
+                         L.step_ntiles);                                                                       \
+  } while (0)
 #define PM_STEP_ALL(SR)                                                                             \
   if (parity) {                                                                                     \
     if (pow) { if (logda) PM_STEP(true, true, true, SR); else PM_STEP(true, true, false, SR); }       \
@@ -578,8 +603,15 @@ hipError_t launch_step_oop(const KParams<T>& src, const KParams<T>& dst, const L
                            bool pow, bool logda) {
   if (!(L.step_w == 64 || L.step_w == 128 || L.step_w == 256) || L.step_w > TILE) return hipErrorInvalidValue;
   dim3 grid(L.step_ntiles), block(L.step_w);
-#define PM_OOP(ODD, POW, LOG, SR) \
-  hipLaunchKernelGGL((k_step_oop<T, ODD, POW, LOG, SR>), grid, block, 0, L.stream, src, dst, L.step_tiles_x)
+#define PM_OOP(ODD, POW, LOG, SR)                                                                           \
+  do {                                                                                                     \
+    if (L.near)                                                                                            \
+      hipLaunchKernelGGL((k_step_oop<T, ODD, POW, LOG, SR, true>), grid, block, 0, L.stream, src, dst,      \
+                         L.step_tiles_x, L.step_ntiles);                                                   \
+    else                                                                                                   \
+      hipLaunchKernelGGL((k_step_oop<T, ODD, POW, LOG, SR, false>), grid, block, 0, L.stream, src, dst,     \
+                         L.step_tiles_x, L.step_ntiles);                                                   \
+  } while (0)
 #define PM_OOP_ALL(SR)                                                                              \
   if (parity) {                                                                                     \
     if (pow) { if (logda) PM_OOP(true, true, true, SR); else PM_OOP(true, true, false, SR); }         \
@@ -603,11 +635,18 @@ hipError_t launch_step_oop(const KParams<T>& src, const KParams<T>& dst, const L
 
 template <typename T>
 hipError_t launch_step_multi(const SweepCase<T>* cases, const int2* sched, const int* live,
-                             int nsched, int parity, int tw, int th, bool any_sr, hipStream_t s) {
+                             int nsched, int parity, int tw, int th, bool any_sr, bool near, hipStream_t s) {
   if (!sweep_tile_ok(tw, th)) return hipErrorInvalidValue;
   if (nsched <= 0) return hipSuccess;  // no live case scheduled
-#define PM_MULTI(ODD, SR) \
-  hipLaunchKernelGGL((k_step_multi<T, ODD, SR>), dim3(nsched), dim3(tw * th), 0, s, cases, sched, live, tw, th)
+#define PM_MULTI(ODD, SR)                                                                                            \
+  do {                                                                                                              \
+    if (near)                                                                                                       \
+      hipLaunchKernelGGL((k_step_multi<T, ODD, SR, true>), dim3(nsched), dim3(tw * th), 0, s, cases, sched, live, tw, \
+                         th);                                                                                       \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_step_multi<T, ODD, SR, false>), dim3(nsched), dim3(tw * th), 0, s, cases, sched, live,   \
+                         tw, th);                                                                                   \
+  } while (0)
   bool sr = false;
   if constexpr (std::is_same<T, float>::value) {
     sr = any_sr;
@@ -772,7 +811,7 @@ hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream
   template hipError_t launch_step_oop<T>(const KParams<T>&, const KParams<T>&, const Launch&, int, \
                                          bool, bool);                                           \
   template hipError_t launch_step_multi<T>(const SweepCase<T>*, const int2*, const int*, int, int, \
-                                           int, int, bool, hipStream_t);                          \
+                                           int, int, bool, bool, hipStream_t);                    \
   template hipError_t launch_resid_multi<T>(const SweepCase<T>*, int, const int2*, int*, int, int, \
                                             int, int, double*, SweepStatus*, int64_t, double,     \
                                             int64_t, hipStream_t);
