@@ -68,7 +68,7 @@ extern "C" {
 #define PM_ROUND_STOCHASTIC 1 /* FP32/FP16 population updates rounded stochastically (see pm_params.rounding) */
 #define PM_ROUND_AUTO 2       /* default: stochastic with FP32 and FP16 storage, nearest with FP64 */
 
-#define PM_STEP_AUTO 0   /* two-step kernel where it pays off (large FP32 cavities) */
+#define PM_STEP_AUTO 0   /* several steps per pass where it pays off (large FP32 and small cavities) */
 #define PM_STEP_SINGLE 1 /* always one step per pass (in place, AA pattern) */
 #define PM_STEP_PAIR 2   /* two steps per pass wherever allowed (FP32, no periodic axis) */
 
@@ -103,10 +103,10 @@ typedef struct {
   double sT_e, sT_nu;     /* D2Q5 higher-moment rates (default 1.0, 1.0) */
   double gx, gy;          /* extra uniform body force, lattice units (default 0) */
   double T_init;          /* initial uniform theta (default 0.5) */
-  int32_t step_kernel;    /* PM_STEP_AUTO (default), PM_STEP_SINGLE or PM_STEP_PAIR.  Both
-                             kernels give the same populations bit for bit; the two-step
-                             kernel needs a second population region in the workspace
-                             (pm_workspace_bytes accounts for it).  PM_STEP_PAIR with FP64,
+  int32_t step_kernel;    /* PM_STEP_AUTO (default), PM_STEP_SINGLE or PM_STEP_PAIR.  All
+                             kernels give the same populations bit for bit; those that take
+                             several steps per pass need a second population region in the
+                             workspace (pm_workspace_bytes accounts for it).  PM_STEP_PAIR with FP64,
                              a periodic axis or ny > 24 * 65535 is PM_EINVAL (PM_STEP_AUTO
                              then takes the single-step kernel). */
   int32_t rounding;       /* PM_ROUND_AUTO (default), PM_ROUND_NEAREST or PM_ROUND_STOCHASTIC (FP32

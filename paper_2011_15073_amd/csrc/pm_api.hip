@@ -44,6 +44,7 @@ struct Layout {
   size_t plane;      // pitch of the per-cell planes (log10 Da, snapshot), elements
   size_t pop_bytes;  // the population region (f and g, padding included)
   size_t off_f, off_g, off_logda, off_snap, off_red, off_scan, total;
+  size_t off_tile;   // second population region of a small cavity (0: none)
   size_t off_pair;   // second population region for the two-step kernel (0: none)
 };
 
@@ -106,6 +107,15 @@ bool pair_capable(const pm_params& p) {
   return wg >= pm::PAIR_MIN_WORKGROUPS;
 }
 
+// Small cavities take several steps per launch (pm::launch_tile) between two
+// population regions.  The second region (at most 15 MB) is part of every
+// workspace of such a grid, whatever the step kernel, so that the size does not
+// depend on it.
+bool tile_capable(const pm_params& p) {
+  if (p.dtype == PM_FP16 || p.periodic_x || p.periodic_y) return false;
+  return (int64_t)p.nx * p.ny <= (p.dtype == PM_FP64 ? pm::TILE_NODES_F64 : pm::TILE_NODES_F32);
+}
+
 Layout layout_of(const pm_params& p, bool pair = false) {
   Layout L{};
   L.elem = p.dtype == PM_FP64 ? 8 : (p.dtype == PM_FP16 ? 2 : 4);
@@ -133,6 +143,10 @@ Layout layout_of(const pm_params& p, bool pair = false) {
   o = align_up(o + (pm::RED_BLOCKS + 16) * sizeof(double));
   L.off_scan = o;  // block sums of the stream-function scan
   o = align_up(o + pm::stream_scratch_bytes(p.nx, p.ny));
+  if (tile_capable(p)) {
+    L.off_tile = o;
+    o = align_up(o + L.pop_bytes);
+  }
   if (pair) {
     o = (o + (size_t(1) << 21) - 1) / (size_t(1) << 21) * (size_t(1) << 21);  // 2 MiB, like the base
     L.off_pair = o;
@@ -287,7 +301,9 @@ struct pm_ctx {
   pm::KParams<float> k32;
   pm::KParams<double> k64;
   pm::KParams<float, _Float16> k16;  // FP16 storage, FP32 compute
-  pm::KParams<float> k32b;  // k32 on the second population region (two-step kernel)
+  pm::KParams<float> k32b;   // k32 and k64 on the second population region (two-step or tile kernel)
+  pm::KParams<double> k64b;
+  pm::TilePlan tile;         // several steps per launch on a small cavity (ts = 0: not used)
   bool pair;                // two-step kernel available (FP32 cavity, second region)
   int pair_rows;            // rows per workgroup of the two-step kernel
   pm::Launch launch;
@@ -321,8 +337,10 @@ hipError_t dispatch(pm_ctx* c, F&& fn) {
 
 // k steps from step count start_steps.  With the two-step kernel, whole
 // groups of four steps from an even step count run as two passes (region
-// A -> B -> A, so the state always ends in its own region); the remaining
-// steps use the single-step kernel in place.
+// A -> B -> A, so the state always ends in its own region); on small cavities
+// whole groups of 2 ts steps run as two launches of the tile kernel in the same
+// way, the last group with what is left.  The remaining steps use the
+// single-step kernel in place.
 hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_steps) {
   pm::Launch L = c->launch;
   L.stream = s;
@@ -338,6 +356,17 @@ hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_step
     for (; e == hipSuccess && k - t >= 4; t += 4) {
       e = pm::launch_step2(c->k32, c->k32b, s, c->pow, logda, c->pair_rows);
       if (e == hipSuccess) e = pm::launch_step2(c->k32b, c->k32, s, c->pow, logda, c->pair_rows);
+    }
+  }
+  if (c->tile.ts) {
+    if ((start_steps & 1) && k > 0) e = single(t++);
+    while (e == hipSuccess && k - t >= 2) {
+      const int ts = (int)std::min<int64_t>(c->tile.ts, (k - t) / 2);
+      for (int back = 0; back < 2 && e == hipSuccess; ++back)
+        e = c->p.dtype == PM_FP64
+                ? pm::launch_tile(back ? c->k64b : c->k64, back ? c->k64 : c->k64b, c->tile, ts, s, c->pow, logda)
+                : pm::launch_tile(back ? c->k32b : c->k32, back ? c->k32 : c->k32b, c->tile, ts, s, c->pow, logda);
+      t += 2 * ts;
     }
   }
   for (; e == hipSuccess && t < k; ++t) e = single(t);
@@ -493,14 +522,18 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
   c->k64 = kparams<double>(*p, L, dev_ws, lay);
   c->k16 = kparams<float, _Float16>(*p, L, dev_ws, lay);
   c->pair = pair;
-  if (pair) {
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) cus = 256;
+  if (pair) c->pair_rows = pair_rows_for(p->nx, p->ny, cus);
+  if (lay.off_tile && !pair && p->step_kernel == PM_STEP_AUTO)
+    c->tile = pm::tile_plan(p->nx, p->ny, p->dtype == PM_FP64, cus);
+  if (const size_t off = pair ? lay.off_pair : lay.off_tile) {
     c->k32b = c->k32;
-    c->k32b.f = (float*)((char*)dev_ws + lay.off_pair + lay.off_f);
-    c->k32b.g = (float*)((char*)dev_ws + lay.off_pair + lay.off_g);
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
-      cus = 256;
-    c->pair_rows = pair_rows_for(p->nx, p->ny, cus);
+    c->k32b.f = (float*)((char*)dev_ws + off + lay.off_f);
+    c->k32b.g = (float*)((char*)dev_ws + off + lay.off_g);
+    c->k64b = c->k64;
+    c->k64b.f = (double*)((char*)dev_ws + off + lay.off_f);
+    c->k64b.g = (double*)((char*)dev_ws + off + lay.off_g);
   }
   c->launch.stream = c->stream;
   c->launch.tiles_x = (p->nx + pm::TILE - 1) / pm::TILE;

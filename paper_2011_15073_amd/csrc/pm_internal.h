@@ -172,6 +172,18 @@ hipError_t launch_fill_zero(double* a, int64_t n, hipStream_t s);
 // the adjoint partials of nblocks workgroups reduced in workgroup order into out[ADJ_PART]
 hipError_t launch_adj_reduce(const double* partial, int nblocks, double* out, hipStream_t s);
 hipError_t launch_write_header(void* dst, int64_t steps, uint64_t tag, uint64_t phys, hipStream_t s);
+// Small cavities (no periodic axis, FP32 or FP64): up to plan.ts steps per
+// launch, tile by tile, from the natural-layout state in src (even step count)
+// to dst (pm_tile.hip).  tile_plan: ts = 0 for a grid above the limits, where
+// one step per launch is as fast.
+constexpr int64_t TILE_NODES_F32 = 520 * 520, TILE_NODES_F64 = 264 * 264;
+struct TilePlan {
+  int w, h, ts;  // region in nodes, most steps per launch
+};
+TilePlan tile_plan(int nx, int ny, bool fp64, int cus);
+template <typename T>
+hipError_t launch_tile(const KParams<T>& src, const KParams<T>& dst, const TilePlan& plan, int ts, hipStream_t s, bool pow,
+                       bool logda);
 // Two time steps of an FP32 cavity (no periodic axis) in one pass, from the
 // natural-layout state in src (even step count) to dst.
 hipError_t launch_step2(const KParams<float>& src, const KParams<float>& dst, hipStream_t s, bool pow,
