@@ -32,8 +32,9 @@ __device__ __forceinline__ int band_of_block(int b, int G) {
 
 // Arithmetic helpers.  FP32 uses the hardware approximations directly
 // (v_rcp_f32, v_exp_f32, v_log_f32, v_sqrt_f32, about 1 ulp): the FP32 path is
-// held to 1e-4 against the FP64 oracle.  FP64 keeps IEEE division and the
-// library exp2 / log2 / sqrt.
+// held to 1e-4 against the FP64 oracle.  FP64 uses the library exp2 / log2 /
+// sqrt and correctly rounded reciprocals: frcp where the argument is of
+// ordinary size by construction, fdiv1 (IEEE division) where it may not be.
 #ifndef PM_FAST_MATH
 #define PM_FAST_MATH 1
 #endif
@@ -52,7 +53,24 @@ template <> __device__ __forceinline__ float flog2<float>(float x) { return log2
 template <> __device__ __forceinline__ float fexp2<float>(float x) { return exp2f(x); }
 template <> __device__ __forceinline__ float fsqrt<float>(float x) { return sqrtf(x); }
 #endif
-template <> __device__ __forceinline__ double frcp<double>(double x) { return 1.0 / x; }
+// 1 / x for x of ordinary size (2^-1000 < |x| < 2^1000): the hardware estimate
+// and Newton's iteration r += r (1 - x r) three times, each residual exact by
+// FMA; the third makes it the correctly rounded quotient.  7 instructions
+// instead of the 11 of a division, whose other four scale extreme arguments:
+// with nine reciprocals per node update 1501 x 1031 FP64 54.5 -> 53.3 us per
+// step, the 27-case FP64 sweep 135.3 -> 134.4.  (The same for the square roots
+// needs a branch for zero velocities and was slower where one wave per SIMD
+// waits for it: 160^2 3.36 -> 3.44 us.)
+template <> __device__ __forceinline__ double frcp<double>(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+template <typename T> __device__ __forceinline__ T fdiv1(T x) {  // 1 / x for any x (FP32: as frcp)
+  if constexpr (std::is_same<T, double>::value) return 1.0 / x;
+  else return frcp<T>(x);
+}
 template <> __device__ __forceinline__ double flog2<double>(double x) { return log2(x); }
 template <> __device__ __forceinline__ double fexp2<double>(double x) { return exp2(x); }
 template <> __device__ __forceinline__ double fsqrt<double>(double x) { return sqrt(x); }
@@ -344,13 +362,21 @@ __device__ __forceinline__ void store_node(const KParams<T, S>& p, int i, int j,
 // two instead of four or five.
 constexpr int NU_FP32_STEPS = 4;
 
+// y clamped to [lo, hi]; a NaN goes to lo.  In FP32 one median instruction
+// instead of three (maximum, minimum, and a canonicalising move before them).
+template <typename T>
+__device__ __forceinline__ T clamp_y(T y, T lo, T hi) {
+  if constexpr (std::is_same<T, float>::value) return __builtin_amdgcn_fmed3f(y, lo, hi);
+  else return fmin(fmax(y, lo), hi);
+}
+
 template <typename T, typename S>
 __device__ __forceinline__ T nu_start(const KParams<T, S>& p, T A, T B) {
   if constexpr (std::is_same<T, double>::value) {
     const float lo = (float)p.y_lo, hi = (float)p.y_hi, lc0 = (float)p.lc0, nm1 = (float)p.nm1;
     const float Af = (float)A, Bf = (float)B;
     float y = (lc0 + nm1 * (0.5f * __builtin_amdgcn_logf(Bf) - 1.5849625007f)) * (float)p.inv_n;
-    y = fminf(fmaxf(y, lo), hi);
+    y = clamp_y(y, lo, hi);
     for (int it = 0; it < NU_FP32_STEPS; ++it) {  // a fixed count: no lane depends on another
       const float nu = __builtin_amdgcn_exp2f(y);
       const float s = __builtin_amdgcn_rcpf(3.0f * nu + 0.5f);
@@ -358,16 +384,17 @@ __device__ __forceinline__ T nu_start(const KParams<T, S>& p, T A, T B) {
       const float G = (y - lc0) - 0.5f * nm1 * __builtin_amdgcn_logf(g2);
       const float dG = 1.0f + 3.0f * nm1 * Bf * s * s * s * nu * __builtin_amdgcn_rcpf(g2);
       const float yn = y - G * __builtin_amdgcn_rcpf(dG);
-      if (g2 > 0.0f && yn == yn) y = fminf(fmaxf(yn, lo), hi);  // no shear in FP32: the FP64 steps decide
+      if (g2 > 0.0f && yn == yn) y = clamp_y(yn, lo, hi);  // no shear in FP32: the FP64 steps decide
     }
-    return fmin(fmax((double)y, p.y_lo), p.y_hi);
+    return clamp_y((double)y, p.y_lo, p.y_hi);
   } else {
     const T y = (p.lc0 + p.nm1 * (T(0.5) * flog2<T>(B) - T(1.584962500721156181453738943947816508))) * p.inv_n;
-    return fmin(fmax(y, p.y_lo), p.y_hi);  // log2(B = 0) = -inf: lands on a bound
+    return clamp_y(y, p.y_lo, p.y_hi);  // log2(B = 0) = -inf: lands on a bound
   }
 }
 
-template <typename T, typename S>
+// FEW: for kernels that run with few waves per SIMD (see the select below).
+template <bool FEW, typename T, typename S>
 __device__ __forceinline__ T solve_nu(const KParams<T, S>& p, T A, T B) {
   const T half = T(0.5);
   const T hn = half * p.nm1;
@@ -379,18 +406,29 @@ __device__ __forceinline__ T solve_nu(const KParams<T, S>& p, T A, T B) {
     const T s2 = s * s;
     const T g2 = A + B * s2;
     const T G = (y - p.lc0) - hn * flog2<T>(g2);
-    const T dG = T(1) + T(3) * p.nm1 * B * s2 * s * nu * frcp<T>(g2);
+    const T dG = T(1) + T(3) * p.nm1 * B * s2 * s * nu * fdiv1<T>(g2);
     T yn = y - G * frcp<T>(dG);
-    // no shear at all (g2 = 0): G = -inf (n < 1) or +inf (n > 1)
-    if (!(g2 > T(0))) yn = G < T(0) ? p.y_hi : p.y_lo;
-    yn = fmin(fmax(yn, p.y_lo), p.y_hi);
+    // no shear at all (g2 = 0): G = -inf (n < 1) or +inf (n > 1).  Rare: behind
+    // a wave-uniform branch it costs one comparison instead of four
+    // instructions (the asm keeps the compiler from turning it back into
+    // selects).  At 4096^2 with FP16 storage a step takes 200 us with the
+    // branch, 210 without; with one or two waves per SIMD the branch is the
+    // longer chain (k_tile at 256^2: 3.13 us against 3.09).
+    const bool shear = g2 > T(0);
+    if (FEW) {
+      yn = shear ? yn : (G < T(0) ? p.y_hi : p.y_lo);
+    } else if (__builtin_amdgcn_ballot_w64(!shear) != 0) {
+      T at = G < T(0) ? p.y_hi : p.y_lo;
+      asm volatile("" : "+v"(at));
+      yn = shear ? yn : at;
+    }
+    yn = clamp_y(yn, p.y_lo, p.y_hi);
     // each lane keeps the first iterate whose step is within the tolerance,
     // so a node's viscosity does not depend on which nodes share its wave
-    if (!conv) {
-      conv = fabs(yn - y) <= p.tol;
-      y = yn;
-    }
-    if (__all(conv)) break;
+    const bool now = fabs(yn - y) <= p.tol;
+    y = conv ? y : yn;
+    conv = conv | now;
+    if (__builtin_amdgcn_ballot_w64(!conv) == 0) break;
   }
   return fexp2<T>(y);
 }
@@ -403,7 +441,7 @@ struct Macro {
 // Steps 2-6 of the update for one node (shifted populations in registers):
 // moments, buoyancy, provisional velocity, viscosity, porous velocity.  ldk:
 // the node's log10(Da) (LOGDA), loaded by the caller with the populations.
-template <typename T, bool POW, bool LOGDA, typename S>
+template <typename T, bool POW, bool LOGDA, bool FEW = false, typename S>
 __device__ __forceinline__ void node_macros(const KParams<T, S>& p, T ldk, const T df[9],
                                             const T dg[5], T& drho, T& rho, T& jx, T& jy,
                                             T& dT, T& Gx, T& Gy, T& nu, T& ux, T& uy, T& invK,
@@ -435,7 +473,7 @@ __device__ __forceinline__ void node_macros(const KParams<T, S>& p, T ldk, const
     const T irho2 = irho * irho;
     const T A = T(0.25) * p.s_e * p.s_e * en * en * irho2;
     const T B = T(2.25) * (pn * pn + T(4) * qn * qn) * irho2;
-    nu = solve_nu(p, A, B);
+    nu = solve_nu<FEW>(p, A, B);
   } else {
     nu = p.nu_newt;
   }
@@ -524,12 +562,12 @@ __device__ __forceinline__ T load_logda(const KParams<T, S>& p, int k) {
 // The full local update: Steps 2-9 on shifted populations, in place.
 // With SR and half storage, *rw receives the node's random word for the
 // stores' stochastic conversion (the caller passes rw then).
-template <typename T, bool POW, bool LOGDA, bool SR = false, typename S>
+template <typename T, bool POW, bool LOGDA, bool SR = false, bool FEW = false, typename S>
 __device__ __forceinline__ void collide(const KParams<T, S>& p, int k, T ldk, T df[9], T dg[5],
                                         unsigned* rw = nullptr) {
   T drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK, invsK, m1, m7, m8;
-  node_macros<T, POW, LOGDA>(p, ldk, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
-                             invsK, m1, m7, m8);
+  node_macros<T, POW, LOGDA, FEW>(p, ldk, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
+                                  invsK, m1, m7, m8);
   // Step 7: force per unit mass (Darcy + Forchheimer drag, eps G)
   const T um = fsqrt<T>(ux * ux + uy * uy);
   const T drag = p.eps * nu * invK + p.eps * p.Feps * invsK * um;

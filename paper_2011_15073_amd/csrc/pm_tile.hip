@@ -96,7 +96,7 @@ __global__ __launch_bounds__(NMAX) void k_tile(KParams<T> src, T* __restrict__ d
   auto step = [&](int t, auto B) __attribute__((always_inline)) {
     T* const L = &buf[decltype(B)::value][0][0];
     if (depth >= t) {
-      collide<T, POW, LOGDA, SR>(src, k, ldk, f, g);
+      collide<T, POW, LOGDA, SR, true>(src, k, ldk, f, g);
 #pragma unroll
       for (int q = 1; q < 9; ++q) L[plane_of(q) * NMAX + tid] = f[q];
 #pragma unroll
