@@ -9,15 +9,15 @@ run-to-steady loop.  W untimed warm-up steps, then K timed steps between two
 synchronisations.
 
 Metric: MLUPS (million node updates per second, flow + thermal).  Also
-reported, for the dominant kernel (the two-step kernel, which advances every
-node by two steps per launch, at 4096^2 FP32):
+reported, for the dominant kernel (the multi-step pass, which advances every
+node by three steps per launch, at 4096^2 FP32):
   * roofline.achieved / frac: the kernel's algorithmic bytes per launch --
     one read and one write of the whole state, 112 B per node (9 + 5 FP32
     populations), for either step kernel -- over the HIP-event-timed launch,
     against the 8 TB/s HBM peak;
   * alg_equiv_GBps / alg_equiv_frac: the method's 112 B per node update times
-    the 2 N^2 updates of a launch over the same time (the single-pass
-    roofline of the method, which the two-step kernel can pass);
+    the 3 N^2 updates of a launch over the same time (the single-pass
+    roofline of the method, which the multi-step pass can exceed);
   * traffic / hbm_GBps / hbm_frac / copy_frac: the HBM bytes the kernel
     really moves per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, committed
     with a hash of the kernel code) over the launch time, against the peak
@@ -54,25 +54,23 @@ CHECK_EVERY = 1000
 DEFAULT_ROUNDING = "stochastic"  # the library's default for FP32 (PM_ROUND_AUTO)
 CSRC = os.path.join(ROOT, "paper_2011_15073_amd", "csrc")
 # The step kernels the benchmark can time (--step-kernel; the default "auto"
-# takes the two-step kernel at 4096^2), each with its committed counter
+# takes the multi-step pass at 4096^2), each with its committed counter
 # summary and the code that decides what it computes and moves: the per-node
 # device code and parameters (whole files), the kernel and its launcher, and
 # the host's launch-shape choice.
 KERNELS = {
     "pair": dict(
-        name="k_step2 (two fused stream+collide steps per launch, LDS row rings)", steps_per_launch=2,
-        traffic_file=os.path.join(ROOT, "profiles", "k_step2_fp32_4096_traffic.txt"),
-        srcs=[os.path.join(CSRC, "pm_device.h"), os.path.join(CSRC, "pm_internal.h"),
-              (os.path.join(CSRC, "pm_kernels.hip"), r"// ---- two time steps in one pass.*?(?=// ---- )"),
-              (os.path.join(CSRC, "pm_kernels.hip"), r"hipError_t launch_step2\(.*?\n}\n"),
-              (os.path.join(CSRC, "pm_api.hip"), r"int pair_rows_for\(.*?\n}\n")]),
+        name="k_march (three fused stream+collide steps per pass, strips of 64 columns in registers)", steps_per_launch=3,
+        traffic_file=os.path.join(ROOT, "profiles", "k_march_fp32_4096_traffic.txt"),
+        srcs=[os.path.join(CSRC, "pm_device.h"), os.path.join(CSRC, "pm_internal.h"), os.path.join(CSRC, "pm_march.hip")]),
     "pair_sr": dict(
-        name="k_step2 SR (two fused steps per launch, stochastically rounded updates)", steps_per_launch=2,
-        traffic_file=os.path.join(ROOT, "profiles", "k_step2_fp32sr_4096_traffic.txt"),
-        srcs=[os.path.join(CSRC, "pm_device.h"), os.path.join(CSRC, "pm_internal.h"),
-              (os.path.join(CSRC, "pm_kernels.hip"), r"// ---- two time steps in one pass.*?(?=// ---- )"),
-              (os.path.join(CSRC, "pm_kernels.hip"), r"hipError_t launch_step2\(.*?\n}\n"),
-              (os.path.join(CSRC, "pm_api.hip"), r"int pair_rows_for\(.*?\n}\n")]),
+        name="k_march SR (three fused steps per pass, stochastically rounded updates)", steps_per_launch=3,
+        traffic_file=os.path.join(ROOT, "profiles", "k_march_fp32sr_4096_traffic.txt"),
+        srcs=[os.path.join(CSRC, "pm_device.h"), os.path.join(CSRC, "pm_internal.h"), os.path.join(CSRC, "pm_march.hip")]),
+    "pair_fp64": dict(
+        name="k_march FP64 (two fused stream+collide steps per pass)", steps_per_launch=2,
+        traffic_file=os.path.join(ROOT, "profiles", "k_march_fp64_4096_traffic.txt"),
+        srcs=[os.path.join(CSRC, "pm_device.h"), os.path.join(CSRC, "pm_internal.h"), os.path.join(CSRC, "pm_march.hip")]),
     "single_sr": dict(
         name="k_step SR (one fused stream+collide step per launch, stochastically rounded updates)",
         steps_per_launch=1,
@@ -509,7 +507,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=200)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--step-kernel", default="auto", choices=["auto", "single", "pair"],
-                    help="step kernel of the cavity (auto: the two-step kernel at 4096^2)")
+                    help="step kernel of the cavity (auto: the multi-step pass at 4096^2)")
     ap.add_argument("--dtype", default="fp32", choices=["fp32", "fp64", "fp16"],
                     help="storage and arithmetic of the timed cavity (fp64: the single-step kernel, 224 B per "
                          "node update; fp16: half-precision population storage with FP32 arithmetic, the "
@@ -590,7 +588,7 @@ def main():
     run = time_cavity(P, S, dt, rounding, args.step_kernel, args.warmup, args.steps, args.roofline_steps)
     mlups, ms_per_step, launch_s = run["mlups"], run["ms_per_step"], run["per_step_s"] * spl
     # algorithmic bytes of one launch of either step kernel: the launch reads
-    # the whole state once and writes it once (the two-step kernel keeps its
+    # the whole state once and writes it once (the multi-step pass keeps its
     # intermediate step on chip), 112 B (FP32) / 224 B (FP64) / 56 B (FP16
     # storage) per node
     alg_launch = bpn * S * S
@@ -674,8 +672,9 @@ def bytes_per_node(dt):
 
 
 def kernel_kind(P, S, dt, step_kernel, rounding):
-    """The step kernel the library will run (only the two-step kernel needs a
-    second population region) and its entry in KERNELS."""
+    """The step kernel the library will run (only the multi-step pass of large
+    grids lets the step kernel decide about a second population region) and
+    its entry in KERNELS."""
     pair = (P.workspace_bytes(P.make_params(S, dtype=dt, step_kernel=step_kernel, **PHYS)) >
             P.workspace_bytes(P.make_params(S, dtype=dt, step_kernel="single", **PHYS)))
     kind = ("pair" if pair else "single") + {"fp64": "_fp64", "fp16": "_fp16"}.get(dt, "")
@@ -688,7 +687,8 @@ def time_cavity(P, S, dt, rounding, step_kernel, warmup, steps, roofline_steps):
     """The timed run: warm-up, then `steps` steps with the on-device Nu and
     residual every CHECK_EVERY steps between two synchronisations; then the
     step time from HIP events on the context's stream around
-    roofline_steps steps (a multiple of 4: whole two-step pairs)."""
+    roofline_steps steps (a multiple of 12: whole rounds of two multi-step
+    passes)."""
     import torch
     cav = P.Cavity(S, dtype=dt, device="cuda:0", step_kernel=step_kernel, rounding=rounding, **PHYS)
     stream = cav.stream
@@ -709,7 +709,7 @@ def time_cavity(P, S, dt, rounding, step_kernel, warmup, steps, roofline_steps):
     nu = nus[-1] if nus else cav.nu()
     log(f"bench: {rounding}: {S * S * steps / elapsed / 1e6:.1f} MLUPS, {elapsed * 1e3 / steps:.4f} ms/step, "
         f"Nu {nu:.6f}")
-    rs = roofline_steps - roofline_steps % 4
+    rs = roofline_steps - roofline_steps % 12
     with torch.cuda.stream(stream):
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)

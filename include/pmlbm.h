@@ -70,7 +70,7 @@ extern "C" {
 
 #define PM_STEP_AUTO 0   /* several steps per pass where it pays off (large FP32 and small cavities) */
 #define PM_STEP_SINGLE 1 /* always one step per pass (in place, AA pattern) */
-#define PM_STEP_PAIR 2   /* two steps per pass wherever allowed (FP32, no periodic axis) */
+#define PM_STEP_PAIR 2   /* several steps per pass wherever allowed (FP32, no periodic axis) */
 
 #define PM_CLAMP_NU 0    /* nu = clamp(nu0 gamma*^(n-1), nu_lo nu0, nu_hi nu0) */
 #define PM_CLAMP_GAMMA 1 /* nu = nu0 clamp(gamma*, nu_lo, nu_hi)^(n-1): the

@@ -31,7 +31,7 @@ void set_global_err(const char* fmt, ...) {
 }
 
 constexpr size_t ALIGN = 256;
-constexpr int GRAPH_PAIRS = 32;  // steps per captured graph = 2 * GRAPH_PAIRS
+constexpr int GRAPH_PAIRS = 30;  // steps per captured graph = 2 * GRAPH_PAIRS (whole groups of 2 x 3 and 2 x 2 steps)
 constexpr uint64_t STATE_TAG = 0x504d4c424d535431ull;  // "PMLBMST1"
 constexpr size_t HEADER_BYTES = 256;
 
@@ -45,7 +45,7 @@ struct Layout {
   size_t pop_bytes;  // the population region (f and g, padding included)
   size_t off_f, off_g, off_logda, off_snap, off_red, off_scan, total;
   size_t off_tile;   // second population region of a small cavity (0: none)
-  size_t off_pair;   // second population region for the two-step kernel (0: none)
+  size_t off_pair;   // second population region for the multi-step pass (0: none)
 };
 
 // Populations are row-interleaved: row j holds the 9 f rows then the 5 g rows
@@ -58,13 +58,6 @@ struct Layout {
 #define PM_SOA_LAYOUT 0
 #endif
 
-// Two time steps per pass (pm::launch_step2) for large FP32 cavities without
-// a periodic axis: fewer HBM bytes per step at the price of a second
-// population region.  PM_PAIR_STEP=0 builds without it, for comparison.
-#ifndef PM_PAIR_STEP
-#define PM_PAIR_STEP 1
-#endif
-
 // Row-segment width of the single-step kernels' workgroups (64, 128 or 256
 // nodes; one lane per node either way, so the results do not depend on it).
 // Measured on one MI355X (us per step, widths 256 / 128 / 64):
@@ -75,36 +68,21 @@ int step_width_for(int nx, int ny, int dtype) {
   return dtype == PM_FP64 ? 128 : 256;
 }
 
-// Rows per workgroup of the two-step kernel: the workgroups run in rounds of
-// PAIR_PER_CU per CU, so a last round that is mostly empty costs nearly a
-// full one; fewer rows recompute a larger share of halo rows (4 extra rows of
-// step k per workgroup).  Pick the row count in [PAIR_R_MIN, PAIR_R] that
-// minimises (rows + 4) / rows divided by the fraction of the last round used.
-int pair_rows_for(int nx, int ny, int cus) {
-  const int64_t strips = (nx + pm::PAIR_W - 1) / pm::PAIR_W, slots = (int64_t)pm::PAIR_PER_CU * cus;
-  int best = pm::PAIR_R;
-  double best_cost = 1e300;
-  for (int r = pm::PAIR_R; r >= pm::PAIR_R_MIN; --r) {
-    if ((ny + r - 1) / r > pm::GRID_Y_MAX) break;  // row groups are gridDim.y
-    const int64_t wg = strips * ((ny + r - 1) / r);
-    const int64_t rounds = (wg + slots - 1) / slots;
-    const double fill = (double)wg / (double)(rounds * slots);
-    const double cost = (double)(r + 4) / r / fill;
-    if (cost < best_cost - 1e-12) {
-      best_cost = cost;
-      best = r;
-    }
-  }
-  return best;
-}
+// Large cavities take several steps per pass (pm::launch_march) between two
+// population regions, when a second one of at most 64 GiB (FP64: 32) covers
+// them; ny up to PAIR_NY_MAX.  The plan for the size is made with 256 CUs, so
+// that the workspace does not depend on the device; PM_STEP_PAIR asks for the
+// pass on any FP32 cavity.
+constexpr int PAIR_NY_MAX = 24 * 65535;
 
 bool pair_capable(const pm_params& p) {
-  if (!PM_PAIR_STEP || p.dtype != PM_FP32 || p.periodic_x || p.periodic_y) return false;
-  if ((p.ny + pm::PAIR_R - 1) / pm::PAIR_R > pm::GRID_Y_MAX) return false;
+  if (p.dtype == PM_FP16 || p.periodic_x || p.periodic_y || p.ny > PAIR_NY_MAX) return false;
   if (p.step_kernel == PM_STEP_PAIR) return true;
   if (p.step_kernel == PM_STEP_SINGLE) return false;
-  const int64_t wg = (int64_t)((p.nx + pm::PAIR_W - 1) / pm::PAIR_W) * ((p.ny + pm::PAIR_R - 1) / pm::PAIR_R);
-  return wg >= pm::PAIR_MIN_WORKGROUPS;
+  const bool fp64 = p.dtype == PM_FP64;
+  const double bytes = 14.0 * (((double)p.nx + 63) / 64 * 64) * p.ny * (fp64 ? 8 : 4);
+  if (bytes > (fp64 ? 32.0 : 64.0) * 1073741824.0) return false;
+  return pm::march_plan(p.nx, p.ny, fp64, p.n != 1.0, 256, false).ts != 0;
 }
 
 // Small cavities take several steps per launch (pm::launch_tile) between two
@@ -190,10 +168,10 @@ int map_params(const pm_params& p, pm_lattice& L, char* msg, size_t msglen) {
     return fail("gx, gy, T_init must be finite");
   if (p.step_kernel != PM_STEP_AUTO && p.step_kernel != PM_STEP_SINGLE && p.step_kernel != PM_STEP_PAIR)
     return fail("step_kernel must be PM_STEP_AUTO, PM_STEP_SINGLE or PM_STEP_PAIR");
-  if (p.step_kernel == PM_STEP_PAIR && (!PM_PAIR_STEP || p.dtype != PM_FP32 || p.periodic_x || p.periodic_y))
+  if (p.step_kernel == PM_STEP_PAIR && (p.dtype != PM_FP32 || p.periodic_x || p.periodic_y))
     return fail("PM_STEP_PAIR needs FP32 and cavity walls on both axes");
-  if (p.step_kernel == PM_STEP_PAIR && (p.ny + pm::PAIR_R - 1) / pm::PAIR_R > pm::GRID_Y_MAX)
-    return fail("PM_STEP_PAIR: ny too large (more row groups than a launch's y dimension takes)");
+  if (p.step_kernel == PM_STEP_PAIR && p.ny > PAIR_NY_MAX)
+    return fail("PM_STEP_PAIR: ny must be <= 24 * 65535");
   if (p.rounding != PM_ROUND_NEAREST && p.rounding != PM_ROUND_STOCHASTIC && p.rounding != PM_ROUND_AUTO)
     return fail("rounding must be PM_ROUND_AUTO, PM_ROUND_NEAREST or PM_ROUND_STOCHASTIC");
   if (p.rounding == PM_ROUND_STOCHASTIC && p.dtype == PM_FP64)
@@ -301,11 +279,10 @@ struct pm_ctx {
   pm::KParams<float> k32;
   pm::KParams<double> k64;
   pm::KParams<float, _Float16> k16;  // FP16 storage, FP32 compute
-  pm::KParams<float> k32b;   // k32 and k64 on the second population region (two-step or tile kernel)
+  pm::KParams<float> k32b;   // k32 and k64 on the second population region (multi-step pass or tile kernel)
   pm::KParams<double> k64b;
   pm::TilePlan tile;         // several steps per launch on a small cavity (ts = 0: not used)
-  bool pair;                // two-step kernel available (FP32 cavity, second region)
-  int pair_rows;            // rows per workgroup of the two-step kernel
+  pm::MarchPlan march;       // several steps per pass on a large cavity (ts = 0: not used)
   pm::Launch launch;
   bool pow;
   hipGraphExec_t graph[2];  // chunk graphs starting at parity 0 / 1
@@ -335,12 +312,12 @@ hipError_t dispatch(pm_ctx* c, F&& fn) {
   return fn(c->k32);
 }
 
-// k steps from step count start_steps.  With the two-step kernel, whole
-// groups of four steps from an even step count run as two passes (region
-// A -> B -> A, so the state always ends in its own region); on small cavities
-// whole groups of 2 ts steps run as two launches of the tile kernel in the same
-// way, the last group with what is left.  The remaining steps use the
-// single-step kernel in place.
+// k steps from step count start_steps.  Where the grid takes several steps per
+// pass (small cavities: the tile kernel, large ones: the multi-step pass),
+// whole groups of 2 ts steps from an even step count run as two passes, region
+// A -> B -> A, so that the state always ends in its own region, the last group
+// with the ts that is left; the remaining steps use the single-step kernel in
+// place.
 hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_steps) {
   pm::Launch L = c->launch;
   L.stream = s;
@@ -349,23 +326,24 @@ hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_step
     const int parity = (int)((start_steps + t) & 1);
     return dispatch(c, [&](auto& kp) { return pm::launch_step(kp, L, parity, c->pow, logda); });
   };
+  auto pass = [&](const auto& from, const auto& to, int ts) {
+    return c->march.ts ? pm::launch_march(from, to, c->march, ts, s, c->pow, logda)
+                       : pm::launch_tile(from, to, c->tile, ts, s, c->pow, logda);
+  };
   hipError_t e = hipSuccess;
   int64_t t = 0;
-  if (c->pair) {
+  if (const int most = c->march.ts ? c->march.ts : c->tile.ts) {
+    const int least = c->march.ts ? 2 : 1;
     if ((start_steps & 1) && k > 0) e = single(t++);
-    for (; e == hipSuccess && k - t >= 4; t += 4) {
-      e = pm::launch_step2(c->k32, c->k32b, s, c->pow, logda, c->pair_rows);
-      if (e == hipSuccess) e = pm::launch_step2(c->k32b, c->k32, s, c->pow, logda, c->pair_rows);
-    }
-  }
-  if (c->tile.ts) {
-    if ((start_steps & 1) && k > 0) e = single(t++);
-    while (e == hipSuccess && k - t >= 2) {
-      const int ts = (int)std::min<int64_t>(c->tile.ts, (k - t) / 2);
-      for (int back = 0; back < 2 && e == hipSuccess; ++back)
-        e = c->p.dtype == PM_FP64
-                ? pm::launch_tile(back ? c->k64b : c->k64, back ? c->k64 : c->k64b, c->tile, ts, s, c->pow, logda)
-                : pm::launch_tile(back ? c->k32b : c->k32, back ? c->k32 : c->k32b, c->tile, ts, s, c->pow, logda);
+    while (e == hipSuccess && k - t >= 2 * least) {
+      const int ts = (int)std::min<int64_t>(most, (k - t) / 2);
+      if (c->p.dtype == PM_FP64) {
+        e = pass(c->k64, c->k64b, ts);
+        if (e == hipSuccess) e = pass(c->k64b, c->k64, ts);
+      } else {
+        e = pass(c->k32, c->k32b, ts);
+        if (e == hipSuccess) e = pass(c->k32b, c->k32, ts);
+      }
       t += 2 * ts;
     }
   }
@@ -485,8 +463,8 @@ int pm_init(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream,
 
 namespace {
 
-// pm_init, with or without the second population region of the two-step
-// kernel (contexts of a sweep go without: the sweep has its own kernels).
+// pm_init, with or without the second population region of the multi-step
+// pass (contexts of a sweep go without: the sweep has its own kernels).
 int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream, bool pair, pm_ctx** out) {
   if (!out) {
     set_global_err("pm_init: null out pointer");
@@ -521,11 +499,10 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
   c->k32 = kparams<float>(*p, L, dev_ws, lay);
   c->k64 = kparams<double>(*p, L, dev_ws, lay);
   c->k16 = kparams<float, _Float16>(*p, L, dev_ws, lay);
-  c->pair = pair;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) cus = 256;
-  if (pair) c->pair_rows = pair_rows_for(p->nx, p->ny, cus);
-  if (lay.off_tile && !pair && p->step_kernel == PM_STEP_AUTO)
+  if (pair) c->march = pm::march_plan(p->nx, p->ny, p->dtype == PM_FP64, c->pow, cus, true);
+  else if (lay.off_tile && p->step_kernel == PM_STEP_AUTO)
     c->tile = pm::tile_plan(p->nx, p->ny, p->dtype == PM_FP64, cus);
   if (const size_t off = pair ? lay.off_pair : lay.off_tile) {
     c->k32b = c->k32;

@@ -102,23 +102,7 @@ constexpr size_t NEAR_BYTES = size_t(256) << 20;
 #endif
 constexpr int TILE = PM_TILE;   // nodes per workgroup (one row segment)
 
-// The two-step kernel: a workgroup owns PAIR_W output columns by PAIR_R
-// output rows.  It pays off only with many workgroups: each marches through
-// its rows with two barriers per row, and only three fit a CU (LDS), so the
-// library uses it when the grid gives at least PAIR_MIN_WORKGROUPS of them
-// (three full rounds of 3 workgroups on each of 256 CUs; at 4096^2 it is 20%
-// faster per step than the single-step kernel, at 3072^2 and below equal or
-// slower).
-// PAIR_R is the nominal row count (the host tunes the actual one per grid
-// between PAIR_R_MIN and PAIR_R so that the workgroups fill whole rounds).
-#ifndef PM_PAIR_R
-#define PM_PAIR_R 24
-#endif
-constexpr int PAIR_W = PM_TILE - 4;
-constexpr int PAIR_R = PM_PAIR_R;
-constexpr int PAIR_R_MIN = 16;
-constexpr int PAIR_PER_CU = 3;  // resident workgroups per CU (LDS: 2 x 24 KB each)
-constexpr int64_t PAIR_MIN_WORKGROUPS = 9 * 256;
+constexpr int MARCH_WAVES = 4;   // strips (waves) per workgroup of the multi-step pass
 constexpr int RED_BLOCKS = 1024; // partial-result slots of the residual
 constexpr int GRID_Y_MAX = 65535; // largest gridDim.y of any launch: taller grids loop over rows
 
@@ -184,10 +168,17 @@ TilePlan tile_plan(int nx, int ny, bool fp64, int cus);
 template <typename T>
 hipError_t launch_tile(const KParams<T>& src, const KParams<T>& dst, const TilePlan& plan, int ts, hipStream_t s, bool pow,
                        bool logda);
-// Two time steps of an FP32 cavity (no periodic axis) in one pass, from the
-// natural-layout state in src (even step count) to dst.
-hipError_t launch_step2(const KParams<float>& src, const KParams<float>& dst, hipStream_t s, bool pow,
-                        bool logda, int rows);
+// Large cavities (no periodic axis, FP32 or FP64): ts time steps in one pass,
+// from the natural-layout state in src (even step count) to dst
+// (pm_march.hip).  march_plan: ts = 0 where one step per pass is faster (not
+// with force); launch_march takes ts = 2, and in FP32 also 3.
+struct MarchPlan {
+  int ts, rows;  // most steps per pass, output rows per workgroup
+};
+MarchPlan march_plan(int nx, int ny, bool fp64, bool pow, int cus, bool force);
+template <typename T>
+hipError_t launch_march(const KParams<T>& src, const KParams<T>& dst, const MarchPlan& plan, int ts, hipStream_t s,
+                        bool pow, bool logda);
 // Stream function up each column, in place on the U field in psi; scratch:
 // stream_scratch_bytes(nx, ny) bytes of device memory.
 size_t stream_scratch_bytes(int nx, int ny);
