@@ -28,9 +28,28 @@ using namespace pm::dev;
 constexpr double LN2 = 0.693147180559945309417232121458176568;
 constexpr double LN10 = 2.302585092994045684017991454684364208;
 
+// sqrt(x) and 1 / sqrt(x) for x of ordinary size, to about an ulp: the hardware
+// estimate and Goldschmidt's iteration twice (10 instructions; the library's
+// square root and a division take 30).
+struct Root {
+  double sqrt, rsqrt;
+};
+__device__ __forceinline__ Root root(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  return Root{g, 2.0 * h};
+}
+
 // Viscosity of one node in FP64 with the data the adjoint needs.
 struct NuSol {
-  double nu, y, s, g2, Gp;
+  double nu, y, s, g2;
   int branch;  // 0: power law (root of G), 1: at nu_min, 2: at nu_max
 };
 
@@ -39,9 +58,8 @@ __device__ __forceinline__ NuSol nu_fp64(const AdjParams& a, double A, double B)
   if (!a.pow) {  // Newtonian: nu = nu0 (the bounds bracket 1), G = y - log2 nu0
     r.y = a.log2nu0;
     r.nu = a.nu0;
-    r.s = 1.0 / (3.0 * r.nu + 0.5);
+    r.s = frcp<double>(3.0 * r.nu + 0.5);
     r.g2 = A + B * r.s * r.s;
-    r.Gp = 1.0;
     r.branch = 0;
     return r;
   }
@@ -56,7 +74,7 @@ __device__ __forceinline__ NuSol nu_fp64(const AdjParams& a, double A, double B)
     // log2(0) = -inf (no shear, or B below the FP32 range) lands on a bound
     yf = (lc0 + nm1 * (0.5f * __builtin_amdgcn_logf(Bf) - 1.5849625007f)) * (float)a.inv_n;
     yf = fminf(fmaxf(yf, lo), hi);
-    for (int it = 0; it < 6; ++it) {
+    for (int it = 0; it < NU_FP32_STEPS; ++it) {
       const float nu = __builtin_amdgcn_exp2f(yf);
       const float sf = __builtin_amdgcn_rcpf(3.0f * nu + 0.5f);
       const float g2 = Af + Bf * sf * sf;
@@ -72,38 +90,48 @@ __device__ __forceinline__ NuSol nu_fp64(const AdjParams& a, double A, double B)
   // max(n, 1) and G'' is of order |n - 1|, so a step of size d leaves an
   // error of order d^2.  A step below 1e-9 therefore ends the iteration
   // (the error left is below 1e-17) without a further step to confirm it;
-  // from the FP32 start that is two FP64 steps.  nu at the last iterate is
-  // then 2^y of the one before times 2^d = 1 + t + t^2/2 (t = d ln 2, the
-  // next term below 1e-28): no further exp2.
-  double nu_last = 0.0, d_last = 0.0;
-  bool conv = false;
+  // from the FP32 start that is two FP64 steps.  nu after the last step is
+  // 2^y of the iterate before times 2^d = 1 + t + t^2/2 (t = d ln 2, the
+  // next term below 1e-28), and s = 1 / (3 nu + 1/2) to first order.
+  // The steps between are small as well, since the start is good to 1e-6: up to
+  // 2^-13 they take 2^d and log2(g2 / g2_old) from their series (the terms left
+  // out are below 1e-19) instead of calling exp2 and log2 again.
+  double nu = exp2(y);
+  double s = frcp<double>(3.0 * nu + 0.5);
+  double g2 = A + B * s * s;
+  double L = log2(g2);
   for (int it = 0; it < 60; ++it) {
-    const double nu = exp2(y);
-    const double s = 1.0 / (3.0 * nu + 0.5);
-    const double g2 = A + B * s * s;
-    const double G = (y - a.lc0) - hn * log2(g2);
-    const double dG = 1.0 + 3.0 * a.nm1 * B * s * s * s * nu / g2;
-    double yn = y - G / dG;
+    const double rg = 1.0 / g2;
+    const double G = (y - a.lc0) - hn * L;
+    const double dG = 1.0 + 3.0 * a.nm1 * B * s * s * s * nu * rg;
+    double yn = y - G * frcp<double>(dG);
     if (!(g2 > 0.0)) yn = G < 0.0 ? a.y_hi : a.y_lo;
     yn = fmin(fmax(yn, a.y_lo), a.y_hi);
-    d_last = yn - y;
-    nu_last = nu;
+    const double d = yn - y, t = d * LN2;
     y = yn;
-    if (fabs(d_last) <= 1e-9) {
-      conv = true;
+    if (fabs(d) <= 1e-9) {
+      const double dnu = nu * (t * (1.0 + 0.5 * t));
+      nu += dnu;
+      s -= 3.0 * dnu * s * s;
       break;
+    }
+    if (fabs(d) < 0x1p-13) {
+      nu *= 1.0 + t * (1.0 + t * (0.5 + t * (1.0 / 6.0 + t * (1.0 / 24.0))));
+      s = frcp<double>(3.0 * nu + 0.5);
+      const double g2n = A + B * s * s, e = (g2n - g2) * rg;
+      L += (1.0 / LN2) * e * (1.0 - e * (0.5 - e * (1.0 / 3.0 - e * (0.25 - e * 0.2))));
+      g2 = g2n;
+    } else {
+      nu = exp2(y);
+      s = frcp<double>(3.0 * nu + 0.5);
+      g2 = A + B * s * s;
+      L = log2(g2);
     }
   }
   r.y = y;
-  if (conv) {
-    const double t = d_last * LN2;
-    r.nu = nu_last * (1.0 + t * (1.0 + 0.5 * t));
-  } else {
-    r.nu = exp2(y);
-  }
-  r.s = 1.0 / (3.0 * r.nu + 0.5);
-  r.g2 = A + B * r.s * r.s;
-  r.Gp = 1.0 + 3.0 * a.nm1 * B * r.s * r.s * r.s * r.nu / r.g2;
+  r.nu = nu;
+  r.s = s;
+  r.g2 = A + B * s * s;
   r.branch = (y <= a.y_lo) ? 1 : ((y >= a.y_hi) ? 2 : 0);
   return r;
 }
@@ -123,7 +151,7 @@ __device__ __forceinline__ void vjp_node(const AdjParams& a, const double df[9],
   const double dT = dg[0] + ((dg[1] + dg[2]) + (dg[3] + dg[4]));
   const double Gx = a.gx;
   const double Gy = a.gy + a.gbeta * (dT - a.dTm);
-  const double irho = 1.0 / rho;
+  const double irho = frcp<double>(rho);
   const double vx = jx * irho + 0.5 * eps * Gx;
   const double vy = jy * irho + 0.5 * eps * Gy;
   const double s14 = (df[1] + df[2]) + (df[3] + df[4]);
@@ -143,25 +171,28 @@ __device__ __forceinline__ void vjp_node(const AdjParams& a, const double df[9],
   double invK, invsK;
   if (a.has_logda) {
     invK = exp2(-3.321928094887362347870319429489390175864831 * logda) * a.inv_Kscale;
-    invsK = sqrt(invK);
+    invsK = root(invK).sqrt;
   } else {
     invK = a.invK;
     invsK = a.invsK;
   }
   const double c0 = 0.5 * (1.0 + 0.5 * eps * nu * invK);
   const double c1 = 0.5 * eps * a.Feps * invsK;
-  const double vm = sqrt(vx * vx + vy * vy);
-  const double sq = sqrt(c0 * c0 + c1 * vm);
-  const double den = c0 + sq;
-  const double iden = 1.0 / den;
+  // |v|, 1 / |v| (0 at rest) and from them |u| and the direction of both
+  const double v2 = vxx + vyy;
+  const bool moves = v2 > 1e-290;
+  const Root rv = root(moves ? v2 : 1.0);
+  const double vm = moves ? rv.sqrt : 0.0, ivm = moves ? rv.rsqrt : 0.0;
+  const Root rq = root(c0 * c0 + c1 * vm);
+  const double iden = frcp<double>(c0 + rq.sqrt);
   const double ux = vx * iden, uy = vy * iden;
-  const double um = sqrt(ux * ux + uy * uy);
+  const double um = vm * iden;
   const double drag = eps * nu * invK + eps * a.Feps * invsK * um;
   const double Fx = eps * Gx - drag * ux;
   const double Fy = eps * Gy - drag * uy;
   const double uu = ux * ux + uy * uy;
   const double uF = ux * Fx + uy * Fy;
-  const double snu = 1.0 / (3.0 * nu + 0.5);
+  const double snu = ns.s;
   const double hnu = 1.0 - 0.5 * snu;
   // (m2, m4, m6 enter the collision linearly: only their adjoints are needed)
   const double P7 = rho * (ux * ux - uy * uy) * ie, Q7 = 2.0 * rho * (ux * Fx - uy * Fy) * ie;
@@ -291,30 +322,21 @@ __device__ __forceinline__ void vjp_node(const AdjParams& a, const double df[9],
   double b_invK = eps * nu * b_drag;
   double b_invsK = eps * a.Feps * um * b_drag;
   const double b_um = eps * a.Feps * invsK * b_drag;
-  if (um > 0.0) {
-    const double ium = 1.0 / um;
-    b_ux += ux * ium * b_um;
-    b_uy += uy * ium * b_um;
-  }
+  const double ex = vx * ivm, ey = vy * ivm;
+  b_ux += ex * b_um;
+  b_uy += ey * b_um;
 
   // Step 6: u = v / (c0 + sqrt(c0^2 + c1 |v|))
   double b_vx = iden * b_ux, b_vy = iden * b_uy;
   const double b_iden = vx * b_ux + vy * b_uy;
   const double b_den = -iden * iden * b_iden;
-  double b_c0 = b_den;
-  const double b_sq = b_den;
-  double b_c1 = 0.0;
-  if (sq > 0.0) {
-    const double isq = 1.0 / sq;
-    b_c0 += c0 * isq * b_sq;
-    b_c1 += 0.5 * vm * isq * b_sq;
-    const double b_vm = 0.5 * c1 * isq * b_sq;
-    if (vm > 0.0) {
-      const double ivm = 1.0 / vm;
-      b_vx += vx * ivm * b_vm;
-      b_vy += vy * ivm * b_vm;
-    }
-  }
+  // (c0 >= 1/2: the root is not zero)
+  const double b_rq = b_den * rq.rsqrt;
+  const double b_c0 = b_den + c0 * b_rq;
+  const double b_c1 = 0.5 * vm * b_rq;
+  const double b_vm = 0.5 * c1 * b_rq;
+  b_vx += ex * b_vm;
+  b_vy += ey * b_vm;
   b_nu += 0.25 * eps * invK * b_c0;
   b_invK += 0.25 * eps * nu * b_c0;
   b_invsK += 0.5 * eps * a.Feps * b_c1;
@@ -329,9 +351,11 @@ __device__ __forceinline__ void vjp_node(const AdjParams& a, const double df[9],
     g_lnnu0 += nu * b_nu;  // nu = bound * nu0
   } else {
     const double b_y = b_nu * nu * LN2;  // nu = 2^y
-    const double w = b_y / ns.Gp;
-    // dy = -(G_A dA + G_B dB + G_L0 dL0 + G_n dn) / G'
+    // dy = -(G_A dA + G_B dB + G_L0 dL0 + G_n dn) / G', with 1 / G' = g2 / (g2 + x)
     constexpr double ILN2 = 1.0 / LN2;
+    const double x = a.pow ? 3.0 * a.nm1 * B * ns.s * ns.s * ns.s * ns.nu : 0.0;
+    const double bg = b_y / (ns.g2 + x);
+    const double w = a.pow ? bg * ns.g2 : b_y;
     g_lnnu0 += w * ILN2;  // L0 = log2 nu0, G_L0 = -1
     // At zero shear (possible only with n = 1, where no clamp is active) the
     // power law is singular in n and its one-sided limits sit on a clamp,
@@ -339,11 +363,10 @@ __device__ __forceinline__ void vjp_node(const AdjParams& a, const double df[9],
     if (ns.g2 > 0.0) {
       // G_n = -log2(gamma*).  At the root G = 0 gives log2(g2) = (y - lc0) / hn
       // (to the root's error over hn; the log is taken where hn is small).
-      const double hn = 0.5 * a.nm1;
-      const double l2g2 = fabs(hn) >= 1e-3 ? (ns.y - a.lc0) / hn : log2(ns.g2);
+      const double l2g2 = a.inv_hn != 0.0 ? (ns.y - a.lc0) * a.inv_hn : log2(ns.g2);
       g_n += w * (a.log2c + 0.5 * l2g2);
       if (ns.g2 > a.g2_floor) {
-        const double wg = w * 0.5 * a.nm1 * ILN2 / ns.g2;
+        const double wg = bg * 0.5 * a.nm1 * ILN2;
         b_A += wg;
         b_B += wg * ns.s * ns.s;
       }
@@ -443,26 +466,65 @@ __device__ __forceinline__ void mu_signs(const AdjParams& a, int i, const L rf[9
   }
 }
 
+// op over the 64 lanes of a wave (all active, values >= 0 or op a sum), in lane
+// 63: rotations within the rows of 16, then the rows' results broadcast upwards.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)w, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(w >> 32), CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <typename Op>
+__device__ __forceinline__ double wave_total(double v, Op op) {
+  constexpr int ROW_ROR = 0x120, BCAST15 = 0x142, BCAST31 = 0x143;
+  v = op(v, dpp<ROW_ROR + 8, 0xf>(v));
+  v = op(v, dpp<ROW_ROR + 4, 0xf>(v));
+  v = op(v, dpp<ROW_ROR + 2, 0xf>(v));
+  v = op(v, dpp<ROW_ROR + 1, 0xf>(v));
+  v = op(v, dpp<BCAST15, 0xa>(v));  // rows 1 and 3 take in rows 0 and 2
+  return op(v, dpp<BCAST31, 0xc>(v));  // rows 2 and 3 take in row 1
+}
+
+// Each wave of a workgroup takes a segment of 64 nodes of a row, the segments of
+// all rows numbered one after the other: no wave idles at the end of a row.  (With
+// a workgroup of four waves per 256 nodes of one row a backward step at 300^2
+// takes 17.1 us instead of 12.6.)
+__host__ __device__ inline int64_t adj_groups(int nx, int ny) {
+  return ((int64_t)((nx + 63) / 64) * ny + TILE / 64 - 1) / (TILE / 64);
+}
+__device__ __forceinline__ bool wave_segment(int nx, int ny, int blk, int& i0, int& j) {
+  const int segs = (nx + 63) / 64;
+  const int s = __builtin_amdgcn_readfirstlane(blk * (TILE / 64) + ((int)threadIdx.x >> 6));
+  j = s / segs;
+  i0 = (s - j * segs) * 64;
+  return j < ny;
+}
+
+// What bounds it on small grids is one wave's chain of FP64 instructions (about
+// 1300) between two memory round trips: 256^2 alone 6.3 us, 7.4 with library
+// square roots, one division per quotient, exp2 and log2 in every Newton step
+// and LDS permutes in the sums.  184 registers, two waves per SIMD; three spill
+// (512^2 28.9 us per backward step against 25.3).
 // ODD: the parity of the step whose state is read (a template parameter, so
 // that each variant's loads are one straight-line sequence).
 template <typename S, typename L, bool ODD>
-__global__ __launch_bounds__(TILE) void k_adjoint(KParams<S> st, AdjParams a,
-                                                  const L* __restrict__ lam_next,
-                                                  L* __restrict__ lam, double* __restrict__ g_logda,
-                                                  double* __restrict__ partial) {
+__device__ __forceinline__ void adjoint_tile(const KParams<S>& st, const AdjParams& a, const L* __restrict__ lam_next,
+                                             L* __restrict__ lam, double* __restrict__ g_logda,
+                                             double* __restrict__ partial, int blk) {
   static_assert(TILE % 64 == 0, "whole waves per workgroup");
   constexpr int NW = TILE / 64;  // waves per workgroup
   __shared__ double red[ADJ_PART][NW];
-  const int tiles_x = (a.nx + TILE - 1) / TILE;
-  const int j = blockIdx.x / tiles_x;
-  const int i = (blockIdx.x - j * tiles_x) * TILE + threadIdx.x;
+  int i0, j;
+  const bool some = wave_segment(a.nx, a.ny, blk, i0, j);
+  const int i = i0 + ((int)threadIdx.x & 63);
   double c_lnnu0 = 0.0, c_n = 0.0, c_sg = 0.0, lmax = 0.0;
   // The workgroup's partials and the node's gradient are read, updated and
   // written back; their reads are issued with the node's loads, so that the
   // end of the wave does not wait on a load.
   double p_old = 0.0;
-  if (threadIdx.x < ADJ_PART) p_old = partial[ADJ_PART * blockIdx.x + threadIdx.x];
-  if (i < a.nx) {
+  if (threadIdx.x < ADJ_PART) p_old = partial[ADJ_PART * (int64_t)blk + threadIdx.x];
+  if (some && i < a.nx) {
     // Loads in this order: lambda_{k+1}, the old gradient, the state (whose
     // wall conditions need their values), log10 Da.  Each wait then covers
     // loads that are all in flight already: one memory round trip.
@@ -482,31 +544,30 @@ __global__ __launch_bounds__(TILE) void k_adjoint(KParams<S> st, AdjParams a,
     mu_signs(a, i, rf, rg, mf, mg);
     double g_ld;
     vjp_node(a, df, dg, ld, mf, mg, lf, lg, g_ld, c_lnnu0, c_n, c_sg);
+    double nan = 0.0;  // turns to NaN with a NaN or an infinity among the values: both count as unbounded
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
       __builtin_nontemporal_store((L)lf[q], &lam[q * nn + k]);
       lmax = fmax(lmax, fabs(lf[q]));
-      if (lf[q] != lf[q]) lmax = INFINITY;  // NaN counts as unbounded
+      nan = __builtin_fma(lf[q], 0.0, nan);
     }
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       __builtin_nontemporal_store((L)lg[q], &lam[(9 + q) * nn + k]);
       lmax = fmax(lmax, fabs(lg[q]));
-      if (lg[q] != lg[q]) lmax = INFINITY;
+      nan = __builtin_fma(lg[q], 0.0, nan);
     }
+    if (nan != nan) lmax = INFINITY;
     if (a.has_logda) g_logda[k] = gl_old + g_ld;
   }
-  // Workgroup sums (and the max): a butterfly over the 64 lanes of each
-  // wave, then the NW wave results in wave order, in one fixed order.
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    c_lnnu0 += __shfl_xor(c_lnnu0, off);
-    c_n += __shfl_xor(c_n, off);
-    c_sg += __shfl_xor(c_sg, off);
-    lmax = fmax(lmax, __shfl_xor(lmax, off));
-  }
+  // Workgroup sums (and the max): over the 64 lanes of each wave by DPP, then
+  // the NW wave results in wave order, in one fixed order.
+  c_lnnu0 = wave_total(c_lnnu0, [](double u, double v) { return u + v; });
+  c_n = wave_total(c_n, [](double u, double v) { return u + v; });
+  c_sg = wave_total(c_sg, [](double u, double v) { return u + v; });
+  lmax = wave_total(lmax, [](double u, double v) { return fmax(u, v); });
   const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
+  if ((threadIdx.x & 63) == 63) {
     red[0][wv] = c_lnnu0;
     red[1][wv] = c_n;
     red[2][wv] = c_sg;
@@ -518,8 +579,47 @@ __global__ __launch_bounds__(TILE) void k_adjoint(KParams<S> st, AdjParams a,
     double v = red[q][0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) v = q < 3 ? v + red[q][w] : fmax(v, red[q][w]);
-    partial[ADJ_PART * blockIdx.x + q] = q < 3 ? p_old + v : fmax(p_old, v);
+    partial[ADJ_PART * (int64_t)blk + q] = q < 3 ? p_old + v : fmax(p_old, v);
   }
+}
+
+template <typename S, typename L, bool ODD>
+__global__ __launch_bounds__(TILE) void k_adjoint(KParams<S> st, AdjParams a, const L* __restrict__ lam_next,
+                                                  L* __restrict__ lam, double* __restrict__ g_logda,
+                                                  double* __restrict__ partial) {
+  adjoint_tile<S, L, ODD>(st, a, lam_next, lam, g_logda, partial, blockIdx.x);
+}
+
+// The adjoint step and, in a second half of the grid (same tiles), one
+// out-of-place forward step src -> dst of another state (src_odd: its parity):
+// the replay of the segment that the adjoint reads next.  A small grid leaves
+// the SIMDs one wave of the adjoint each, which waits most of the time; one
+// launch per step pair instead of two also halves what the host has to submit.
+// Backward, us per step, two launches on two streams / one (FP32 state): 100^2
+// 8.5 / 7.1, 160^2 9.4 / 7.6, 256^2 9.5 / 8.7, 360^2 18.9 / 17.6, 420^2 22 / 22,
+// 512^2 25.3 / 26.2; FP64 state: 100^2 8.4 / 7.2, 200^2 10.2 / 9.5, 256^2 10.1 ..
+// 10.8 / 10.7, 300^2 14.2 / 15.4.
+template <typename S, typename L, bool ODD, bool POW, bool LOGDA>
+__global__ __launch_bounds__(TILE) void k_adjoint_replay(KParams<S> st, AdjParams a, const L* __restrict__ lam_next,
+                                                         L* __restrict__ lam, double* __restrict__ g_logda,
+                                                         double* __restrict__ partial, int nadj, KParams<S> src,
+                                                         KParams<S> dst, int src_odd) {
+  if ((int)blockIdx.x < nadj) {
+    adjoint_tile<S, L, ODD>(st, a, lam_next, lam, g_logda, partial, blockIdx.x);
+    return;
+  }
+  const int blk = (int)blockIdx.x - nadj;
+  int i0, j;
+  if (!wave_segment(a.nx, a.ny, blk, i0, j)) return;
+  if constexpr (std::is_same<S, float>::value) {
+    if (src.sr) {
+      if (src_odd) step_tile<S, true, POW, LOGDA, true, true>(src, dst, i0, j, threadIdx.x & 63);
+      else step_tile<S, false, POW, LOGDA, true, true>(src, dst, i0, j, threadIdx.x & 63);
+      return;
+    }
+  }
+  if (src_odd) step_tile<S, true, POW, LOGDA, false, true>(src, dst, i0, j, threadIdx.x & 63);
+  else step_tile<S, false, POW, LOGDA, false, true>(src, dst, i0, j, threadIdx.x & 63);
 }
 
 // lambda_T = dJ/dS_T for J = Nu_bar (Eq. 24): only the thermal populations of
@@ -579,13 +679,25 @@ hipError_t launch_adj_reduce(const double* partial, int nblocks, double* out, hi
 
 template <typename S, typename L>
 hipError_t launch_adjoint(const KParams<S>& st, const AdjParams& a, int parity, const L* lam_next, L* lam,
-                          double* g_logda, double* partial, hipStream_t s) {
-  const int tiles_x = (a.nx + TILE - 1) / TILE;
+                          double* g_logda, double* partial, hipStream_t s, const Replay<S>* rp) {
+  const int n = (int)adj_groups(a.nx, a.ny);
+  if (rp) {
+#define PM_R(ODD, POW, LOG)                                                                                         \
+  hipLaunchKernelGGL((k_adjoint_replay<S, L, ODD, POW, LOG>), dim3(2 * n), dim3(TILE), 0, s, st, a, lam_next, lam,   \
+                     g_logda, partial, n, rp->src, rp->dst, rp->parity)
+#define PM_R_ALL(ODD)                                                                      \
+  if (a.pow) { if (a.has_logda) PM_R(ODD, true, true); else PM_R(ODD, true, false); }       \
+  else { if (a.has_logda) PM_R(ODD, false, true); else PM_R(ODD, false, false); }
+    if (parity) { PM_R_ALL(true) } else { PM_R_ALL(false) }
+#undef PM_R_ALL
+#undef PM_R
+    return hipGetLastError();
+  }
   if (parity)
-    hipLaunchKernelGGL((k_adjoint<S, L, true>), dim3(tiles_x * a.ny), dim3(TILE), 0, s, st, a, lam_next, lam,
+    hipLaunchKernelGGL((k_adjoint<S, L, true>), dim3(n), dim3(TILE), 0, s, st, a, lam_next, lam,
                        g_logda, partial);
   else
-    hipLaunchKernelGGL((k_adjoint<S, L, false>), dim3(tiles_x * a.ny), dim3(TILE), 0, s, st, a, lam_next, lam,
+    hipLaunchKernelGGL((k_adjoint<S, L, false>), dim3(n), dim3(TILE), 0, s, st, a, lam_next, lam,
                        g_logda, partial);
   return hipGetLastError();
 }
@@ -600,11 +712,11 @@ hipError_t launch_adjoint_seed(int nx, int ny, double seed, L* lam, hipStream_t 
 }
 
 template hipError_t launch_adjoint<float, double>(const KParams<float>&, const AdjParams&, int, const double*,
-                                                  double*, double*, double*, hipStream_t);
+                                                  double*, double*, double*, hipStream_t, const Replay<float>*);
 template hipError_t launch_adjoint<float, float>(const KParams<float>&, const AdjParams&, int, const float*,
-                                                 float*, double*, double*, hipStream_t);
+                                                 float*, double*, double*, hipStream_t, const Replay<float>*);
 template hipError_t launch_adjoint<double, double>(const KParams<double>&, const AdjParams&, int, const double*,
-                                                   double*, double*, double*, hipStream_t);
+                                                   double*, double*, double*, hipStream_t, const Replay<double>*);
 template hipError_t launch_adjoint_seed<double>(int, int, double, double*, hipStream_t);
 template hipError_t launch_adjoint_seed<float>(int, int, double, float*, hipStream_t);
 

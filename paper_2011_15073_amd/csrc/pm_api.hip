@@ -1345,6 +1345,7 @@ pm::AdjParams adj_params(const pm_ctx* c) {
   a.nm1 = p.n - 1.0;
   a.inv_n = 1.0 / p.n;
   a.log2c = std::log2(L.gamma_scale);
+  a.inv_hn = std::fabs(a.nm1) >= 2e-3 ? 2.0 / a.nm1 : 0.0;
   a.lc0 = a.log2nu0 + a.nm1 * a.log2c;
   a.g2_floor = 0.0;
   return a;
@@ -1366,21 +1367,35 @@ int adj_fail(pm_adjoint* a, int code, const char* fmt, ...) {
   return code;
 }
 
-// One adjoint step at a raw state (parity given), lam_next -> lam.
-hipError_t adj_step(const pm_ctx* c, const pm::AdjParams& ap, char* state, int parity, const double* lam_next,
-                    double* lam, double* g_logda, double* partial) {
-  if (c->p.dtype == PM_FP64)
-    return pm::launch_adjoint<double, double>(slot_params<double>(c, c->k64, state), ap, parity, lam_next, lam,
-                                              g_logda, partial, c->stream);
-  return pm::launch_adjoint<float, double>(slot_params<float>(c, c->k32, state), ap, parity, lam_next, lam,
-                                           g_logda, partial, c->stream);
-}
+// Grids of at most this many nodes take the adjoint step and the replay's
+// forward step in one launch (measured on both sides at k_adjoint_replay).
+constexpr int64_t ADJ_FUSED_F32 = 131072, ADJ_FUSED_F64 = 50000;
 
+// A forward step from one raw state to another, for a launch of the adjoint to
+// take along (src null: none).
+struct ReplayStep {
+  char *src, *dst;
+  int parity;
+};
+
+// One adjoint step at a raw state (parity given), lam_next -> lam.
+template <typename S, typename L>
+hipError_t adj_step(const pm_ctx* c, const pm::KParams<S>& base, const pm::AdjParams& ap, char* state, int parity,
+                    const L* lam_next, L* lam, double* g_logda, double* partial, const ReplayStep& r) {
+  pm::Replay<S> rp;
+  if (r.src) rp = pm::Replay<S>{slot_params<S>(c, base, r.src), slot_params<S>(c, base, r.dst), r.parity};
+  return pm::launch_adjoint<S, L>(slot_params<S>(c, base, state), ap, parity, lam_next, lam, g_logda, partial, c->stream,
+                                  r.src ? &rp : nullptr);
+}
+hipError_t adj_step(const pm_ctx* c, const pm::AdjParams& ap, char* state, int parity, const double* lam_next,
+                    double* lam, double* g_logda, double* partial, const ReplayStep& r = ReplayStep{}) {
+  if (c->p.dtype == PM_FP64) return adj_step(c, c->k64, ap, state, parity, lam_next, lam, g_logda, partial, r);
+  return adj_step(c, c->k32, ap, state, parity, lam_next, lam, g_logda, partial, r);
+}
 // The same with an FP32-stored adjoint state (FP32 forward states only).
 hipError_t adj_step(const pm_ctx* c, const pm::AdjParams& ap, char* state, int parity, const float* lam_next,
-                    float* lam, double* g_logda, double* partial) {
-  return pm::launch_adjoint<float, float>(slot_params<float>(c, c->k32, state), ap, parity, lam_next, lam,
-                                          g_logda, partial, c->stream);
+                    float* lam, double* g_logda, double* partial, const ReplayStep& r = ReplayStep{}) {
+  return adj_step(c, c->k32, ap, state, parity, lam_next, lam, g_logda, partial, r);
 }
 
 // Chain rule from the per-node parameters (ln nu0, n at fixed nu0, s_g) to
@@ -1478,8 +1493,7 @@ int pm_adjoint_forward(pm_adjoint* a, double* J_out) {
   a->s0 = c->steps;
   const size_t stride = align_up(a->span);
   for (int64_t k = 0; k < a->ncp; ++k) {
-    hipError_t e = hipMemcpyAsync(a->cp + k * stride, (char*)c->ws + c->lay.off_f, a->span,
-                                  hipMemcpyDeviceToDevice, c->stream);
+    hipError_t e = pm::launch_copy_probe((char*)c->ws + c->lay.off_f, a->cp + k * stride, a->span, c->stream);
     if (e != hipSuccess) return adj_fail(a, PM_EDEVICE, "checkpoint copy: %s", hipGetErrorString(e));
     const int64_t n = std::min(a->C, a->T - k * a->C);
     int rc = pm_step(c, n);
@@ -1507,56 +1521,66 @@ int pm_adjoint_backward(pm_adjoint* a, double seed, void* grad_logda, double* gr
   if (e != hipSuccess) return adj_fail(a, PM_EDEVICE, "backward setup: %s", hipGetErrorString(e));
   const size_t stride = align_up(a->span);
   const bool logda = c->p.has_logda != 0;
-  // Replay of segment k: from its checkpoint, out of place, into C + 1 slots
-  // (slot t holds S_{kC + t}), on the replay stream.
+  // Replay of segment k: from its checkpoint, out of place; slot t of the
+  // segment buffer then holds S_{kC + t} (slot 0 is the checkpoint itself), t
+  // below the segment's length.
+  auto slot = [&](int64_t k, char* seg, int64_t t) { return t == 0 ? a->cp + k * stride : seg + t * stride; };
+  auto length = [&](int64_t k) { return std::min(a->C, a->T - k * a->C); };
+  auto replay_step = [&](int64_t k, char* seg, int64_t t) {
+    return ReplayStep{slot(k, seg, t), slot(k, seg, t + 1), (int)((a->s0 + k * a->C + t) & 1)};
+  };
   pm::Launch rl = c->launch;
-  rl.stream = a->replay;
-  auto replay = [&](int64_t k, char* seg) -> hipError_t {
-    const int64_t start = k * a->C;
-    const int64_t n = std::min(a->C, a->T - start);
-    hipError_t r = hipMemcpyAsync(seg, a->cp + k * stride, a->span, hipMemcpyDeviceToDevice, a->replay);
-    for (int64_t t = 0; t < n && r == hipSuccess; ++t) {
-      const int parity = (int)((a->s0 + start + t) & 1);
-      char* src = seg + t * stride;
-      char* dst = seg + (t + 1) * stride;
+  auto replay = [&](int64_t k, char* seg, int64_t from, hipStream_t s) -> hipError_t {
+    rl.stream = s;
+    hipError_t r = hipSuccess;
+    for (int64_t t = from; t + 1 < length(k) && r == hipSuccess; ++t) {
+      const ReplayStep q = replay_step(k, seg, t);
       if (c->p.dtype == PM_FP64)
-        r = pm::launch_step_oop(slot_params<double>(c, c->k64, src), slot_params<double>(c, c->k64, dst), rl,
-                                parity, c->pow, logda);
+        r = pm::launch_step_oop(slot_params<double>(c, c->k64, q.src), slot_params<double>(c, c->k64, q.dst), rl,
+                                q.parity, c->pow, logda);
       else
-        r = pm::launch_step_oop(slot_params<float>(c, c->k32, src), slot_params<float>(c, c->k32, dst), rl,
-                                parity, c->pow, logda);
+        r = pm::launch_step_oop(slot_params<float>(c, c->k32, q.src), slot_params<float>(c, c->k32, q.dst), rl,
+                                q.parity, c->pow, logda);
     }
     return r;
   };
-  // The replay of segment k - 1 runs while the adjoint steps of segment k
-  // run on the context's stream: buffer b holds segment k, b ^ 1 receives
-  // k - 1 once segment k + 1's adjoint steps have finished reading it.
-  if (e == hipSuccess) e = hipEventRecord(a->ev_start, c->stream);
-  if (e == hipSuccess) e = hipStreamWaitEvent(a->replay, a->ev_start, 0);
-  if (e == hipSuccess) e = replay(a->ncp - 1, a->seg[0]);
-  if (e == hipSuccess) e = hipEventRecord(a->ev_rep[0], a->replay);
+  // Segment k - 1 is replayed while the adjoint steps of segment k run: buffer b
+  // holds segment k, b ^ 1 receives k - 1 once segment k + 1's adjoint steps have
+  // finished reading it.  On small grids the two go into one launch per step,
+  // otherwise the replay has a stream of its own.
+  const bool fused = nn <= (c->p.dtype == PM_FP64 ? ADJ_FUSED_F64 : ADJ_FUSED_F32);
+  hipStream_t rs = fused ? c->stream : a->replay;
+  if (e == hipSuccess && !fused) e = hipEventRecord(a->ev_start, c->stream);
+  if (e == hipSuccess && !fused) e = hipStreamWaitEvent(rs, a->ev_start, 0);
+  if (e == hipSuccess) e = replay(a->ncp - 1, a->seg[0], 0, rs);
+  if (e == hipSuccess && !fused) e = hipEventRecord(a->ev_rep[0], rs);
   int cur = 0;
   for (int64_t k = a->ncp - 1; k >= 0 && e == hipSuccess; --k) {
     const int b = (int)((a->ncp - 1 - k) & 1);
-    if (k >= 1) {
-      if (k + 1 <= a->ncp - 1) e = hipStreamWaitEvent(a->replay, a->ev_used[b ^ 1], 0);
-      if (e == hipSuccess) e = replay(k - 1, a->seg[b ^ 1]);
-      if (e == hipSuccess) e = hipEventRecord(a->ev_rep[b ^ 1], a->replay);
+    char* const next = a->seg[b ^ 1];
+    if (!fused) {
+      if (k >= 1) {
+        if (k + 1 <= a->ncp - 1) e = hipStreamWaitEvent(rs, a->ev_used[b ^ 1], 0);
+        if (e == hipSuccess) e = replay(k - 1, next, 0, rs);
+        if (e == hipSuccess) e = hipEventRecord(a->ev_rep[b ^ 1], rs);
+      }
+      if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, a->ev_rep[b], 0);
     }
-    if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, a->ev_rep[b], 0);
     // adjoint steps in reverse over the segment
-    const int64_t start = k * a->C;
-    const int64_t n = std::min(a->C, a->T - start);
+    const int64_t n = length(k);
     for (int64_t t = n - 1; t >= 0 && e == hipSuccess; --t) {
-      const int parity = (int)((a->s0 + start + t) & 1);
-      char* st = a->seg[b] + t * stride;
+      const int parity = (int)((a->s0 + k * a->C + t) & 1);
+      char* st = slot(k, a->seg[b], t);
+      const bool with = fused && k >= 1 && n - t < length(k - 1);
+      const ReplayStep r = with ? replay_step(k - 1, next, n - 1 - t) : ReplayStep{};
       e = lam32 ? adj_step(c, a->ap, st, parity, (const float*)a->lam[cur], (float*)a->lam[cur ^ 1],
-                           (double*)grad_logda, a->partial)
+                           (double*)grad_logda, a->partial, r)
                 : adj_step(c, a->ap, st, parity, (const double*)a->lam[cur], (double*)a->lam[cur ^ 1],
-                           (double*)grad_logda, a->partial);
+                           (double*)grad_logda, a->partial, r);
       cur ^= 1;
     }
-    if (e == hipSuccess) e = hipEventRecord(a->ev_used[b], c->stream);
+    if (e == hipSuccess && fused && k >= 1) e = replay(k - 1, next, n, rs);  // the last segment may be shorter
+    if (e == hipSuccess && !fused) e = hipEventRecord(a->ev_used[b], c->stream);
   }
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(a->replay);

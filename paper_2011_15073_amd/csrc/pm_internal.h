@@ -79,6 +79,7 @@ struct AdjParams {
   double eps, inv_eps, Feps, invK, invsK, inv_Kscale, gbeta, dTm, gx, gy;
   double s_e, s_eps, s_q, s_g, sT_e, sT_nu, T_ref;
   double nu0, log2nu0, y_lo, y_hi, lc0, nm1, inv_n, log2c;
+  double inv_hn;    // 2 / (n - 1), or 0 where |n - 1| < 2e-3
   double g2_floor;  // (shear-rate floor)^2, lattice units: below it nu is held fixed
 };
 
@@ -145,10 +146,16 @@ template <typename T>
 hipError_t launch_resid_multi(const SweepCase<T>* cases, int ncases, const int2* sched, int* live,
                               int nsched, int parity, int tw, int th, double* partial, SweepStatus* st,
                               int64_t chunk, double tol, int64_t max_steps, hipStream_t s);
-// L: storage type of the adjoint state (double; float for FP32 states)
+// L: storage type of the adjoint state (double; float for FP32 states).  rp: a
+// forward step src -> dst (parity: of src) that the same launch takes besides.
+template <typename S>
+struct Replay {
+  KParams<S> src, dst;
+  int parity;
+};
 template <typename S, typename L>
 hipError_t launch_adjoint(const KParams<S>& st, const AdjParams& a, int parity, const L* lam_next, L* lam,
-                          double* g_logda, double* partial, hipStream_t s);
+                          double* g_logda, double* partial, hipStream_t s, const Replay<S>* rp = nullptr);
 template <typename L>
 hipError_t launch_adjoint_seed(int nx, int ny, double seed, L* lam, hipStream_t s);
 // a[0, n) := 0 (a fill kernel, so that callers may capture it in a graph)
