@@ -43,7 +43,7 @@ struct Layout {
   size_t qs, rs;     // population stride, row stride (elements), see pm::KParams
   size_t plane;      // pitch of the per-cell planes (log10 Da, snapshot), elements
   size_t pop_bytes;  // the population region (f and g, padding included)
-  size_t off_f, off_g, off_logda, off_snap, off_red, off_scan, total;
+  size_t off_f, off_g, off_logda, off_snap, off_scan, total;
   size_t off_tile;   // second population region of a small cavity (0: none)
   size_t off_pair;   // second population region for the multi-step pass (0: none)
 };
@@ -117,8 +117,6 @@ Layout layout_of(const pm_params& p, bool pair = false) {
   if (p.has_logda) o = align_up(o + L.plane * L.pelem);
   L.off_snap = o;
   o = align_up(o + L.plane * L.pelem);
-  L.off_red = o;
-  o = align_up(o + (pm::RED_BLOCKS + 16) * sizeof(double));
   L.off_scan = o;  // block sums of the stream-function scan
   o = align_up(o + pm::stream_scratch_bytes(p.nx, p.ny));
   if (tile_capable(p)) {
@@ -267,6 +265,52 @@ pm::KParams<T, S> kparams(const pm_params& p, const pm_lattice& L, void* ws, con
 
 }  // namespace
 
+namespace {
+
+// Pinned host memory that a kernel writes its RED_BLOCKS partial results to and
+// the host reads after the stream: no copy (which costs a kernel and a staging
+// buffer: pm_nu at 64^2 takes 17 us, 26 with the copy).  Freeing such memory waits for the whole device, so up to
+// HOST_SLOTS_KEPT blocks of destroyed contexts are kept for the next ones; every
+// use ends with a synchronisation of its stream, so a kept block has no writer.
+// Allocation is allowed while some stream is being captured.
+constexpr size_t HOST_SLOTS_KEPT = 64;
+std::mutex host_slots_mutex;
+double* host_slots_kept[HOST_SLOTS_KEPT];
+size_t host_slots_n = 0;
+
+hipError_t host_slots_get(double** p) {
+  {
+    std::lock_guard<std::mutex> lock(host_slots_mutex);
+    if (host_slots_n) {
+      *p = host_slots_kept[--host_slots_n];
+      return hipSuccess;
+    }
+  }
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  e = hipHostMalloc((void**)p, pm::RED_BLOCKS * sizeof(double), hipHostMallocPortable);
+  if (e != hipSuccess) *p = nullptr;
+  const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+  return e == hipSuccess ? back : e;
+}
+
+void host_slots_put(double* p) {
+  {
+    std::lock_guard<std::mutex> lock(host_slots_mutex);
+    if (host_slots_n < HOST_SLOTS_KEPT) {
+      host_slots_kept[host_slots_n++] = p;
+      return;
+    }
+  }
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+  (void)hipHostFree(p);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
+}  // namespace
+
 struct pm_ctx {
   pm_params p;
   pm_lattice L;
@@ -286,7 +330,7 @@ struct pm_ctx {
   pm::Launch launch;
   bool pow;
   hipGraphExec_t graph[2];  // chunk graphs starting at parity 0 / 1
-  double* red;              // device partials + results
+  double* host;             // pinned: partial results of the Nusselt number and the residual
   char err[512];
 };
 
@@ -370,12 +414,6 @@ int build_graph(pm_ctx* c, int parity) {
     return check_hip(c, e, "hipGraphInstantiate");
   }
   return PM_OK;
-}
-
-int sync_read(pm_ctx* c, double* host, const double* dev, int n) {
-  hipError_t e = hipMemcpyAsync(host, dev, n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  return check_hip(c, e, "reading a reduction result");
 }
 
 int dtype_ok(int d) { return d == PM_FP32 || d == PM_FP64; }  // caller-facing arrays
@@ -519,11 +557,16 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
   c->launch.step_tiles_x = (p->nx + c->launch.step_w - 1) / c->launch.step_w;
   c->launch.step_ntiles = c->launch.step_tiles_x * p->ny;
   c->launch.near = lay.pop_bytes <= pm::NEAR_BYTES;
-  c->red = (double*)((char*)dev_ws + lay.off_red);
   hipError_t e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
   if (e != hipSuccess) {
     set_global_err("hipStreamCreateWithFlags: %s", hipGetErrorString(e));
     delete c;
+    return PM_EDEVICE;
+  }
+  e = host_slots_get(&c->host);
+  if (e != hipSuccess) {
+    set_global_err("pinned host memory: %s", hipGetErrorString(e));
+    pm_destroy(c);
     return PM_EDEVICE;
   }
   const double dg_init = (1.0 / 6.0) * (p->T_init - 0.5);
@@ -535,12 +578,12 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
     e = dispatch(c, [&](auto& kp) {
       using T = typename std::remove_reference_t<decltype(kp)>::compute_t;
       T* snap = (T*)((char*)c->ws + c->lay.off_snap);
-      return pm::launch_residual(kp, c->launch, 0, snap, c->red, c->red + pm::RED_BLOCKS, 1);
+      int n = 0;
+      return pm::launch_residual(kp, c->launch, 0, snap, c->host, &n, 1);
     });
   if (e != hipSuccess) {
     set_global_err("pm_init: %s", hipGetErrorString(e));
-    (void)hipStreamDestroy(c->cap_stream);
-    delete c;
+    pm_destroy(c);
     return PM_EDEVICE;
   }
   *out = c;
@@ -556,6 +599,7 @@ void pm_destroy(pm_ctx* c) {
   for (auto& g : c->graph)
     if (g) (void)hipGraphExecDestroy(g);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+  if (c->host) host_slots_put(c->host);
   delete c;
 }
 
@@ -602,11 +646,14 @@ int pm_steps_done(const pm_ctx* c, int64_t* steps) {
 int pm_nu(pm_ctx* c, double* nu_out) {
   if (!c || !nu_out) return PM_EINVAL;
   const int parity = (int)(c->steps & 1);
-  double* dev = c->red + pm::RED_BLOCKS + 1;
-  hipError_t e = dispatch(c, [&](auto& kp) { return pm::launch_nu(kp, c->launch, parity, dev); });
+  int n = 0;
+  hipError_t e = dispatch(c, [&](auto& kp) { return pm::launch_nu(kp, c->launch, parity, c->host, &n); });
   if (e != hipSuccess) return check_hip(c, e, "pm_nu");
-  int rc = sync_read(c, nu_out, dev, 1);
-  if (rc) return rc;
+  e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return check_hip(c, e, "reading a reduction result");
+  double sum = 0.0;
+  for (int b = 0; b < n; ++b) sum += c->host[b];
+  *nu_out = sum / (double)c->p.ny;
   if (!std::isfinite(*nu_out)) return ctx_fail(c, PM_EDIVERGED, "pm_nu: Nusselt number is not finite");
   return PM_OK;
 }
@@ -615,15 +662,16 @@ int pm_residual(pm_ctx* c, double* r_out, int64_t* at_step) {
   if (!c || !r_out) return PM_EINVAL;
   if (at_step) *at_step = c->steps;
   const int parity = (int)(c->steps & 1);
-  double* dev = c->red + pm::RED_BLOCKS;
+  int n = 0;
   hipError_t e = dispatch(c, [&](auto& kp) {
     using T = typename std::remove_reference_t<decltype(kp)>::compute_t;
     T* snap = (T*)((char*)c->ws + c->lay.off_snap);
-    return pm::launch_residual(kp, c->launch, parity, snap, c->red, dev, 0);
+    return pm::launch_residual(kp, c->launch, parity, snap, c->host, &n, 0);
   });
   if (e != hipSuccess) return check_hip(c, e, "pm_residual");
-  int rc = sync_read(c, r_out, dev, 1);
-  if (rc) return rc;
+  e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return check_hip(c, e, "reading a reduction result");
+  *r_out = *std::max_element(c->host, c->host + n);
   if (!std::isfinite(*r_out)) return ctx_fail(c, PM_EDIVERGED, "pm_residual: NaN/Inf in the temperature field");
   return PM_OK;
 }

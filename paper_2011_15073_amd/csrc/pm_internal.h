@@ -104,7 +104,7 @@ constexpr size_t NEAR_BYTES = size_t(256) << 20;
 constexpr int TILE = PM_TILE;   // nodes per workgroup (one row segment)
 
 constexpr int MARCH_WAVES = 4;   // strips (waves) per workgroup of the multi-step pass
-constexpr int RED_BLOCKS = 1024; // partial-result slots of the residual
+constexpr int RED_BLOCKS = 1024; // partial-result slots of the Nusselt number and the residual
 constexpr int GRID_Y_MAX = 65535; // largest gridDim.y of any launch: taller grids loop over rows
 
 // parity 0: state in natural layout; 1: after an odd number of steps
@@ -115,11 +115,13 @@ hipError_t launch_step_oop(const KParams<T>& src, const KParams<T>& dst, const L
                            bool pow, bool logda);
 template <typename T, typename S>
 hipError_t launch_init(const KParams<T, S>& p, const Launch& L, T dg_init, size_t pop_bytes);
+// nu and residual: one value per workgroup into partial[0, *n), *n at most
+// RED_BLOCKS; the Nusselt number is their sum over ny, the residual their maximum.
 template <typename T, typename S>
-hipError_t launch_nu(const KParams<T, S>& p, const Launch& L, int parity, double* out);
+hipError_t launch_nu(const KParams<T, S>& p, const Launch& L, int parity, double* partial, int* n);
 template <typename T, typename S>
-hipError_t launch_residual(const KParams<T, S>& p, const Launch& L, int parity, T* snap,
-                           double* partial, double* out, int take_snapshot_only);
+hipError_t launch_residual(const KParams<T, S>& p, const Launch& L, int parity, T* snap, double* partial, int* n,
+                           int take_snapshot_only);
 template <typename T, typename S>
 hipError_t launch_fields(const KParams<T, S>& p, const Launch& L, int parity, bool pow, bool logda,
                          void* U, void* V, void* th, void* nu, int out_fp64);

@@ -113,12 +113,16 @@ __global__ void k_init(KParams<T, S> p, T dg_init) {
   }
 }
 
-// Eq. (24): one workgroup, fixed summation order (deterministic).
+// Eq. (24): one wave per 64 rows (and per further 64 NU_BLOCKS), its sum into
+// its slot of partial; the host adds the slots in order, so the order of
+// summation is fixed.  Every value read is in a cache line of its own, so that
+// the rows are spread over the CUs: 2048 rows took 35 us by one workgroup of 256,
+// pm_nu 59 us; like this pm_nu takes 18 us at any size up to 4096^2.
 template <typename T, typename S>
-__global__ __launch_bounds__(256) void k_nu(KParams<T, S> p, int parity, double* out) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(64) void k_nu(KParams<T, S> p, int parity, double* __restrict__ partial) {
   double acc = 0.0;
-  for (int j = threadIdx.x; j < p.ny; j += 256) {
+  for (int64_t j0 = (int64_t)blockIdx.x * 64 + threadIdx.x; j0 < p.ny; j0 += (int64_t)gridDim.x * 64) {
+    const int j = (int)j0;
     T g0[5], g1[5];
     if (parity) {
       load_g<T, true>(p, 0, j, g0);
@@ -131,58 +135,59 @@ __global__ __launch_bounds__(256) void k_nu(KParams<T, S> p, int parity, double*
     const double t1 = (double)p.T_ref + (double)(g1[0] + ((g1[1] + g1[2]) + (g1[3] + g1[4])));
     acc += (double)p.nx * (8.0 - 9.0 * t0 + t1) / 3.0;
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0] / (double)p.ny;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off);
+  if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// Residual: per-block max |theta - snapshot|, snapshot := theta.
+// max over the workgroup's threads, in thread 0 (values >= 0).
+__device__ __forceinline__ double block_max(double mx) {
+  __shared__ double red[TILE / 64];
+  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_down(mx, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < ((int)blockDim.x + 63) / 64; ++w) mx = fmax(mx, red[w]);
+  return mx;
+}
+
+// Residual: per-workgroup max |theta - snapshot|, snapshot := theta.  Each wave
+// takes RESID_SEGS segments of 64 nodes of a row at a time, so that their loads
+// are in flight together: it is bound by those, 5 + 1 values read and one
+// written per node.  us per call, 1 / 2 / 4 segments: 2048^2 FP32 30.6 / 31.0 /
+// 30.5, 4096^2 FP32 odd step count 111 / 108 / 100, 3000^2 FP64 102 / 104 / 106
+// (one thread per node with 64-bit divisions, and the maximum by a second
+// kernel and a copy: 41, 121 and 117).
+constexpr int RESID_SEGS = 2;
 template <typename T, typename S>
-__global__ __launch_bounds__(256) void k_resid(KParams<T, S> p, int parity, T* snap,
-                                               double* partial, int snapshot_only) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(256) void k_resid(KParams<T, S> p, int parity, T* __restrict__ snap,
+                                               double* __restrict__ partial, int snapshot_only) {
   double mx = 0.0;
-  const int64_t n = (int64_t)p.nx * p.ny;
-  for (int64_t k = blockIdx.x * (int64_t)256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
-    const int j = (int)(k / p.nx), i = (int)(k - (int64_t)j * p.nx);
-    T g[5];
-    if (parity) load_g<T, true>(p, i, j, g); else load_g<T, false>(p, i, j, g);
-    const T dT = g[0] + ((g[1] + g[2]) + (g[3] + g[4]));
-    double d = fabs((double)dT - (double)snap[k]);
-    if (!(d <= 1.7976931348623157e308)) d = INFINITY;  // NaN / Inf -> +Inf
-    mx = d > mx ? d : mx;
-    snap[k] = dT;
-  }
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      const double o = red[threadIdx.x + s];
-      red[threadIdx.x] = o > red[threadIdx.x] ? o : red[threadIdx.x];
+  const int segs = (p.nx + 63) / 64, lane = threadIdx.x & 63;
+  const int n = segs * p.ny;  // at most the number of nodes, below 2^30
+  const int s0 = ((int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * RESID_SEGS;
+  for (int s = s0; s < n; s += (int)gridDim.x * 4 * RESID_SEGS) {
+    T g[RESID_SEGS][5], old[RESID_SEGS];
+    int64_t k[RESID_SEGS];
+    bool in[RESID_SEGS];
+#pragma unroll
+    for (int t = 0; t < RESID_SEGS; ++t) {  // no branches: a lane past the end repeats the last node
+      const int st = min(s + t, n - 1), j = st / segs, i = (st - j * segs) * 64 + lane, ic = min(i, p.nx - 1);
+      in[t] = s + t < n && i < p.nx;
+      k[t] = (int64_t)j * p.nx + ic;
+      if (parity) load_g<T, true>(p, ic, j, g[t]); else load_g<T, false>(p, ic, j, g[t]);
+      old[t] = snap[k[t]];
     }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = snapshot_only ? 0.0 : red[0];
-}
-
-__global__ __launch_bounds__(256) void k_max_final(const double* partial, int n, double* out) {
-  __shared__ double red[256];
-  double mx = 0.0;
-  for (int b = threadIdx.x; b < n; b += 256) mx = partial[b] > mx ? partial[b] : mx;
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      const double o = red[threadIdx.x + s];
-      red[threadIdx.x] = o > red[threadIdx.x] ? o : red[threadIdx.x];
+#pragma unroll
+    for (int t = 0; t < RESID_SEGS; ++t) {
+      const T dT = g[t][0] + ((g[t][1] + g[t][2]) + (g[t][3] + g[t][4]));
+      double d = fabs((double)dT - (double)old[t]);
+      if (!(d <= 1.7976931348623157e308)) d = INFINITY;  // NaN / Inf -> +Inf
+      mx = in[t] && d > mx ? d : mx;
+      if (in[t]) snap[k[t]] = dT;
     }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0];
+  mx = block_max(mx);
+  if (threadIdx.x == 0 && !snapshot_only) partial[blockIdx.x] = mx;
 }
 
 // Sweep residual: one workgroup per schedule entry (a tile of a live case,
@@ -193,7 +198,6 @@ __global__ __launch_bounds__(TILE) void k_resid_multi(const SweepCase<T>* __rest
                                                       const int2* __restrict__ sched,
                                                       const int* __restrict__ live, int parity,
                                                       double* __restrict__ partial, int tw, int th) {
-  __shared__ double red[TILE];
   const int2 e = sched[blockIdx.x];
   if (!live[e.x]) return;  // uniform over the workgroup
   const SweepCase<T>& c = cases[e.x];
@@ -211,39 +215,30 @@ __global__ __launch_bounds__(TILE) void k_resid_multi(const SweepCase<T>* __rest
     mx = d;
     c.snap[k] = dT;
   }
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = (int)blockDim.x / 2; s > 0; s >>= 1) {  // blockDim.x = tw * th, a power of two
-    if ((int)threadIdx.x < s) {
-      const double o = red[threadIdx.x + s];
-      red[threadIdx.x] = o > red[threadIdx.x] ? o : red[threadIdx.x];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[c.tile_base + e.y] = red[0];
+  mx = block_max(mx);
+  if (threadIdx.x == 0) partial[c.tile_base + e.y] = mx;
 }
 
 // Stopping test of every live case after a chunk of steps: r = max over the
 // case's tiles; the case stops when r < tol, when r is not finite, or when
-// it has reached max_steps.  One workgroup, one thread per case.
+// it has reached max_steps.  One workgroup per case (a thread per case took
+// 104 us for the 27-case sweep, a chain of up to 2048 loads).
 template <typename T>
-__global__ void k_retire(const SweepCase<T>* __restrict__ cases, int ncases,
-                         const double* __restrict__ partial, int* __restrict__ live,
-                         SweepStatus* __restrict__ st, int64_t chunk, double tol,
-                         int64_t max_steps) {
-  for (int c = threadIdx.x; c < ncases; c += blockDim.x) {
-    if (!live[c]) continue;
-    const SweepCase<T>& cs = cases[c];
-    double r = 0.0;
-    for (int b = 0; b < cs.ntiles; ++b) {
-      const double v = partial[cs.tile_base + b];
-      r = v > r ? v : r;
-    }
-    st[c].steps += chunk;
-    st[c].residual = r;
-    const bool finite = r <= 1.7976931348623157e308;
-    if (r < tol || !finite || st[c].steps >= max_steps) live[c] = 0;
-  }
+__global__ __launch_bounds__(TILE) void k_retire(const SweepCase<T>* __restrict__ cases,
+                                                 const double* __restrict__ partial, int* __restrict__ live,
+                                                 SweepStatus* __restrict__ st, int64_t chunk, double tol,
+                                                 int64_t max_steps) {
+  const int c = blockIdx.x;
+  if (!live[c]) return;  // uniform over the workgroup
+  const SweepCase<T>& cs = cases[c];
+  double r = 0.0;
+  for (int b = threadIdx.x; b < cs.ntiles; b += TILE) r = fmax(r, partial[cs.tile_base + b]);
+  r = block_max(r);
+  if (threadIdx.x) return;
+  st[c].steps += chunk;
+  st[c].residual = r;
+  const bool finite = r <= 1.7976931348623157e308;
+  if (r < tol || !finite || st[c].steps >= max_steps) live[c] = 0;
 }
 
 template <typename T, bool ODD, bool POW, bool LOGDA, typename O, typename S>
@@ -258,10 +253,13 @@ __global__ __launch_bounds__(TILE) void k_fields(KParams<T, S> p, O* U, O* V, O*
     T drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK, invsK, m1, m7, m8;
     node_macros<T, POW, LOGDA>(p, ldk, df, dg, drho, rho, jx, jy, dT, Gx, Gy, nu, ux, uy, invK,
                                invsK, m1, m7, m8);
-    if (U) U[k] = (O)(ux * p.inv_U);
-    if (V) V[k] = (O)(uy * p.inv_U);
-    if (th) th[k] = (O)(p.T_ref + dT);
-    if (nuo) nuo[k] = (O)nu;
+    // Streaming stores leave the state in the caches (4096^2 FP32, three fields:
+    // 207 -> 193 us); U alone is for the stream function, whose scan reads it next.
+    if (U && V) __builtin_nontemporal_store((O)(ux * p.inv_U), &U[k]);
+    else if (U) U[k] = (O)(ux * p.inv_U);
+    if (V) __builtin_nontemporal_store((O)(uy * p.inv_U), &V[k]);
+    if (th) __builtin_nontemporal_store((O)(p.T_ref + dT), &th[k]);
+    if (nuo) __builtin_nontemporal_store((O)nu, &nuo[k]);
   }
 }
 
@@ -275,6 +273,9 @@ __device__ __forceinline__ T w5(int q) {
   return q == 0 ? T(1.0 / 3.0) : T(1.0 / 6.0);
 }
 
+// Bound by its traffic, one read and one write of the state.  Streaming stores
+// leave the state in the caches: 2048^2 FP32 98 -> 84 us at an odd step count,
+// 4096^2 344 -> 325.
 template <typename T, bool ODD, typename O, typename S>
 __global__ __launch_bounds__(TILE) void k_get_pop(KParams<T, S> p, O* f, O* g) {
   const int i = blockIdx.x * TILE + threadIdx.x;
@@ -285,9 +286,11 @@ __global__ __launch_bounds__(TILE) void k_get_pop(KParams<T, S> p, O* f, O* g) {
     load_node<T, ODD>(p, i, j, df, dg);
     const int64_t k = (int64_t)j * p.nx + i;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) f[q * n + k] = (O)((double)df[q] + (double)w9<T>(q));
+    for (int q = 0; q < 9; ++q)
+      __builtin_nontemporal_store((O)((double)df[q] + (double)w9<T>(q)), &f[q * n + k]);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) g[q * n + k] = (O)((double)dg[q] + (double)w5<T>(q) * (double)p.T_ref);
+    for (int q = 0; q < 5; ++q)
+      __builtin_nontemporal_store((O)((double)dg[q] + (double)w5<T>(q) * (double)p.T_ref), &g[q * n + k]);
   }
 }
 
@@ -336,6 +339,12 @@ inline int psi_rows(int ny) {
   return r;
 }
 
+// Rows whose loads are in flight together: a column's block is a chain of memory
+// round trips otherwise, and there are few waves (2048^2: one per SIMD).  Stream
+// function of a 1024^2 FP32 state with groups of 8 / 16 / 32: 38.0 / 36.3 / 35.7
+// us, 501^2 31.4 / 29.8 / 32.8 (stores between the loads: 43.2 and 35.6).
+constexpr int PSI_GROUP = 16;
+
 template <typename O>
 __global__ __launch_bounds__(256) void k_psi_blocks(const O* __restrict__ u, double* __restrict__ blk, int nx,
                                                     int ny, int R) {
@@ -343,7 +352,7 @@ __global__ __launch_bounds__(256) void k_psi_blocks(const O* __restrict__ u, dou
   if (i >= nx) return;
   const int j1 = (int)min((int64_t)ny, (int64_t)(b + 1) * R);
   double s = 0.0;
-#pragma unroll 8
+#pragma unroll PSI_GROUP
   for (int j = b * R; j < j1; ++j) s += (double)u[(int64_t)j * nx + i];
   blk[(int64_t)b * nx + i] = s;
 }
@@ -375,12 +384,15 @@ __global__ __launch_bounds__(256) void k_psi_apply(O* __restrict__ psi, const do
   if (i >= nx) return;
   const int j1 = (int)min((int64_t)ny, (int64_t)(b + 1) * R);
   double acc = blk[(int64_t)b * nx + i];
-#pragma unroll 8
-  for (int j = b * R; j < j1; ++j) {
-    const int64_t k = (int64_t)j * nx + i;
-    const double u = (double)psi[k];
-    psi[k] = (O)((acc + 0.5 * u) * inv_L);
-    acc += u;
+  for (int j = b * R; j < j1; j += PSI_GROUP) {
+    O u[PSI_GROUP];  // all loads of a group before its first store (the field is overwritten in place)
+#pragma unroll
+    for (int t = 0; t < PSI_GROUP; ++t) u[t] = psi[(int64_t)min(j + t, j1 - 1) * nx + i];
+#pragma unroll
+    for (int t = 0; t < PSI_GROUP; ++t) {
+      if (j + t < j1) psi[(int64_t)(j + t) * nx + i] = (O)((acc + 0.5 * (double)u[t]) * inv_L);
+      acc += (double)u[t];
+    }
   }
 }
 
@@ -507,8 +519,8 @@ hipError_t launch_resid_multi(const SweepCase<T>* cases, int ncases, const int2*
   if (nsched <= 0) return hipSuccess;  // no live case scheduled
   hipLaunchKernelGGL((k_resid_multi<T>), dim3(nsched), dim3(tw * th), 0, s, cases, sched,
                      (const int*)live, parity, partial, tw, th);
-  hipLaunchKernelGGL((k_retire<T>), dim3(1), dim3(64), 0, s, cases, ncases, (const double*)partial,
-                     live, st, chunk, tol, max_steps);
+  hipLaunchKernelGGL((k_retire<T>), dim3(ncases), dim3(TILE), 0, s, cases, (const double*)partial, live, st,
+                     chunk, tol, max_steps);
   return hipGetLastError();
 }
 
@@ -523,18 +535,17 @@ hipError_t launch_init(const KParams<T, S>& p, const Launch& L, T dg_init, size_
 }
 
 template <typename T, typename S>
-hipError_t launch_nu(const KParams<T, S>& p, const Launch& L, int parity, double* out) {
-  hipLaunchKernelGGL((k_nu<T, S>), dim3(1), dim3(256), 0, L.stream, p, parity, out);
+hipError_t launch_nu(const KParams<T, S>& p, const Launch& L, int parity, double* partial, int* n) {
+  *n = std::min((p.ny + 63) / 64, RED_BLOCKS);
+  hipLaunchKernelGGL((k_nu<T, S>), dim3(*n), dim3(64), 0, L.stream, p, parity, partial);
   return hipGetLastError();
 }
 
 template <typename T, typename S>
-hipError_t launch_residual(const KParams<T, S>& p, const Launch& L, int parity, T* snap,
-                           double* partial, double* out, int snapshot_only) {
-  const int nb = grid_for((int64_t)p.nx * p.ny, 256, RED_BLOCKS);
-  hipLaunchKernelGGL((k_resid<T, S>), dim3(nb), dim3(256), 0, L.stream, p, parity, snap, partial,
-                     snapshot_only);
-  hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, L.stream, (const double*)partial, nb, out);
+hipError_t launch_residual(const KParams<T, S>& p, const Launch& L, int parity, T* snap, double* partial, int* n,
+                           int snapshot_only) {
+  *n = grid_for((int64_t)((p.nx + 63) / 64) * p.ny, 4 * RESID_SEGS, RED_BLOCKS);
+  hipLaunchKernelGGL((k_resid<T, S>), dim3(*n), dim3(256), 0, L.stream, p, parity, snap, partial, snapshot_only);
   return hipGetLastError();
 }
 
@@ -634,9 +645,9 @@ hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream
 #define PM_INST_S(T, S)                                                                          \
   template hipError_t launch_step<T, S>(const KParams<T, S>&, const Launch&, int, bool, bool);    \
   template hipError_t launch_init<T, S>(const KParams<T, S>&, const Launch&, T, size_t);          \
-  template hipError_t launch_nu<T, S>(const KParams<T, S>&, const Launch&, int, double*);         \
+  template hipError_t launch_nu<T, S>(const KParams<T, S>&, const Launch&, int, double*, int*);   \
   template hipError_t launch_residual<T, S>(const KParams<T, S>&, const Launch&, int, T*, double*, \
-                                            double*, int);                                         \
+                                            int*, int);                                            \
   template hipError_t launch_fields<T, S>(const KParams<T, S>&, const Launch&, int, bool, bool,   \
                                           void*, void*, void*, void*, int);                        \
   template hipError_t launch_get_pop<T, S>(const KParams<T, S>&, const Launch&, int, void*, void*, \
