@@ -244,7 +244,8 @@ int pm_copy_probe(const void* src, void* dst, size_t bytes, void* hip_stream);
 /* ---- Batched parameter sweep ----
  * Many independent cavities (e.g. the (n, Da, Ra) grid of the paper's
  * parametric study, Table 2, with uneven grid sides) advanced together: one
- * launch per time step covers every tile of every case still running,
+ * launch per time step covers every tile of every case still running (of
+ * a group of cases, where their states exceed the last-level cache together),
  * and a chunk of check_every steps plus the per-case residual test is
  * replayed as one HIP graph.  Each case stops at the first check with
  * residual < tol (or at max_steps, or on NaN/Inf) exactly as

@@ -71,9 +71,9 @@ __global__ __launch_bounds__(TILE) void k_step_oop(KParams<T> src, KParams<T> ds
 // whatever the tile shape.  SR_ANY: some case rounds stochastically (FP32
 // only); without it the kernel carries no stochastic-rounding branch, which
 // would cost round-to-nearest sweeps registers and occupancy.  NEAR (as in
-// k_step): the live cases' states fit the last-level cache together.  The 27
-// FP32 cases (185 MB): 56.5 us per step near, 62.2 streaming; in FP64 (370 MB)
-// near would be 141 against 130.
+// k_step): the states of the cases in this launch fit the last-level cache
+// together.  27 FP32 cases (185 MB): 56.5 us per step near, 62.2 streaming; in
+// FP64 (370 MB in one launch) near would be 141 against 130.
 template <typename T, bool ODD, bool SR_ANY, bool NEAR>
 __global__ __launch_bounds__(TILE) void k_step_multi(const SweepCase<T>* __restrict__ cases,
                                                      const int2* __restrict__ sched,
