@@ -13,14 +13,14 @@
 // per-node arithmetic is the single-step kernel's (collide): the populations
 // are the same bit for bit.
 //
-// Measured (n = 0.8, stochastic rounding, us per step; one step per pass / the
+// Measured (n = 0.8, stochastic rounding, us per step; one step per pass / an
 // earlier two-step kernel with LDS row rings / this one with TS = 3):
-// 2048^2 66 / 73 / 58, 3000^2 166 / 167 / 118, 4096^2 299 / 230 / 193, 8192^2
-// 1243 / 855 / 730.  FP64 with TS = 2: 3000^2 345 / - / 321, 4096^2 619 / - /
-// 553.  At TS = 3 FP32 the VALU issues 99% of the time (SQ_INSTS_VALU, 436
-// instructions per node update with the overlaps, of which 360 per row and
-// stage), at TS = 2 the pass moves 2.3 GB at 4 TB/s (4096^2 221 us), at TS = 4
-// the registers no longer hold (240).
+// 2048^2 66 / 73 / 58, 3000^2 166 / 167 / 110, 4096^2 299 / 230 / 183 .. 199,
+// 8192^2 1243 / 855 / 628.  FP64 with TS = 2: 3000^2 345 / - / 321, 4096^2 608 /
+// - / 551.  At TS = 3 FP32 the VALU issues all the time (SQ_INSTS_VALU, 410
+// instructions per node update with the overlaps, of which 350 per row and
+// stage; 333 and 285 with round-to-nearest), at TS = 2 the pass moves 2.3 GB at
+// 4 TB/s (4096^2 221 us), at TS = 4 the registers no longer hold (240).
 //
 // What the details are worth at 4096^2:
 //   * the four waves of a workgroup hold adjacent strips and meet at a barrier
@@ -293,7 +293,12 @@ int march_strips(int nx, int ts) { return nx <= 64 ? 1 : (nx - 64 + (64 - 2 * ts
 //            FP64 1100^2 36.7 .. 40 / 38.3, 1300^2 50 .. 55 / 46.6, 2400^2 215 / 135
 //   n = 0.8: FP32 1760^2 45 .. 50 / 47 .. 55, 2200^2 79 .. 84 / 67 .. 88,
 //            2400^2 100 / 79 .. 102, 2600^2 112 .. 118 / 92 .. 119, 4096^2 293 / 195 .. 205;
-//            FP64 2600^2 246 .. 260 / 209 .. 249, 3000^2 342 .. 357 / 291 .. 350, 4096^2 608 / 561
+//            FP64 2600^2 246 .. 260 / 209 .. 249, 3000^2 342 .. 357 / 291 .. 350,
+//            4096^2 607 .. 623 / 551 .. 578, 6000^2 1440 .. 1462 / 915 .. 1324
+// In the few hundred steps in which a flow from rest sets in, FP64 waves at n < 1
+// need the most Newton steps and this pass is the slower one (4096^2 n = 0.8 753
+// against 710, n = 0.6 931 against 809); a run of 3000 steps from rest is still
+// 8% faster with it.
 // Narrow grids leave the last workgroup's waves without strips.
 //
 // Rows: a workgroup of R output rows collides ts R + ts (ts + 1) rows, and
