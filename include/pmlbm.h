@@ -32,8 +32,10 @@
  *   - Device memory is always owned by the caller: the workspace passed to
  *     pm_init, and every output buffer.  The library allocates only its host
  *     context, one private non-blocking stream on which pm_step captures its
- *     HIP graphs, and those graphs, all released by pm_destroy (a sweep or
- *     an adjoint likewise releases what it creates in its own destroy call).
+ *     HIP graphs, those graphs, and 8 KB of pinned host memory for results,
+ *     all released by pm_destroy (a sweep or an adjoint likewise releases
+ *     what it creates in its own destroy call); up to 64 of the pinned blocks
+ *     are kept for later contexts.
  *   - A context is bound to the HIP stream given to pm_init; every call
  *     enqueues on that stream.  Calls that return host values (pm_nu,
  *     pm_residual, pm_run_to_steady) synchronise that stream.  A context is
@@ -68,7 +70,7 @@ extern "C" {
 #define PM_ROUND_STOCHASTIC 1 /* FP32/FP16 population updates rounded stochastically (see pm_params.rounding) */
 #define PM_ROUND_AUTO 2       /* default: stochastic with FP32 and FP16 storage, nearest with FP64 */
 
-#define PM_STEP_AUTO 0   /* several steps per pass where it pays off (large FP32 and small cavities) */
+#define PM_STEP_AUTO 0   /* several steps per pass where it pays off (large and small cavities) */
 #define PM_STEP_SINGLE 1 /* always one step per pass (in place, AA pattern) */
 #define PM_STEP_PAIR 2   /* several steps per pass wherever allowed (FP32, no periodic axis) */
 
