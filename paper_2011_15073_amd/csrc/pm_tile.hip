@@ -138,7 +138,13 @@ constexpr int TILE_TOP_F32 = 1024, TILE_TOP_F64 = 768;  // largest regions (regi
 // grids on which this kernel is the faster one.  With W waves of 64 threads on
 // each SIMD of the fullest CU a launch takes F + b W + ts (c + d W) us; the
 // constants are fitted to 48^2 .. 512^2 in FP32 (F 1.8, b 0.55, c 0.55, d 0.53;
-// within 10%) and 48^2 .. 256^2 in FP64 (2.0, 0.6, 0.85, 1.4).
+// within 10%) and 48^2 .. 256^2 in FP64 (2.0, 0.6, 0.85, 1.4).  A workgroup of
+// more than 512 threads (FP64: 256) has a CU to itself, and each further round of
+// them starts with its loads exposed.  Near the FP32 limit the plan is compared
+// with one step per launch, 2.9 us + 16.2 ps per node.  n = 0.8, us per step, one
+// step / this kernel: 460^2 6.7 / 6.1, 500^2 7.0 / 6.7, 510^2 7.0 / 7.2, 520^2
+// 7.9 / 7.4, 400 x 650 7.4 / 6.1, 650 x 400 7.5 / 7.5, 130 x 2000 8.1 / 7.4 (without
+// the rounds in the model the regions chosen took 6.4, 6.6, 7.6, 8.0, 6.2, 8.7, 9.0).
 TilePlan tile_plan(int nx, int ny, bool fp64, int cus) {
   TilePlan best{0, 0, 0};
   if ((int64_t)nx * ny > (fp64 ? TILE_NODES_F64 : TILE_NODES_F32)) return best;
@@ -151,7 +157,9 @@ TilePlan tile_plan(int nx, int ny, bool fp64, int cus) {
       for (int ts = 2; ts <= 8 && 2 * ts < w && 2 * ts < h; ++ts) {
         const int64_t tiles = tiles_along(nx, w, ts) * tiles_along(ny, h, ts);
         const double waves = (double)((tiles + cus - 1) / cus) * (n / 64) / 4.0;
-        const double us = (F + b * waves) / ts + c + d * waves;
+        const int fit = fp64 ? (n <= 256 ? 2 : 1) : (n <= 256 ? 5 : n <= 512 ? 3 : 1);  // workgroups on a CU at a time
+        const int64_t rounds = (tiles + (int64_t)cus * fit - 1) / ((int64_t)cus * fit);
+        const double us = (F + (double)(rounds - 1) * (F + 1.2) + b * waves) / ts + c + d * waves;
         if (us < best_us) {
           best_us = us;
           best = TilePlan{w, h, ts};
@@ -159,6 +167,7 @@ TilePlan tile_plan(int nx, int ny, bool fp64, int cus) {
       }
     }
   }
+  if (!fp64 && best_us > 6.0 && best_us > 1.02 * (2.9 + 16.2e-6 * (double)nx * ny)) return TilePlan{0, 0, 0};
   return best;
 }
 
