@@ -86,12 +86,14 @@ bool pair_capable(const pm_params& p) {
 }
 
 // Small cavities take several steps per launch (pm::launch_tile) between two
-// population regions.  The second region (at most 15 MB) is part of every
+// population regions.  The second region (at most TILE_BYTES) is part of every
 // workspace of such a grid, whatever the step kernel, so that the size does not
 // depend on it.
 bool tile_capable(const pm_params& p) {
   if (p.dtype == PM_FP16 || p.periodic_x || p.periodic_y) return false;
-  return (int64_t)p.nx * p.ny <= (p.dtype == PM_FP64 ? pm::TILE_NODES_F64 : pm::TILE_NODES_F32);
+  const bool fp64 = p.dtype == PM_FP64;
+  const size_t bytes = 14 * (((size_t)p.nx + 63) / 64 * 64) * (size_t)p.ny * (fp64 ? 8 : 4);
+  return (int64_t)p.nx * p.ny <= (fp64 ? pm::TILE_NODES_F64 : pm::TILE_NODES_F32) && bytes <= pm::TILE_BYTES;
 }
 
 Layout layout_of(const pm_params& p, bool pair = false) {
@@ -541,7 +543,7 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) cus = 256;
   if (pair) c->march = pm::march_plan(p->nx, p->ny, p->dtype == PM_FP64, c->pow, cus, true);
   else if (lay.off_tile && p->step_kernel == PM_STEP_AUTO)
-    c->tile = pm::tile_plan(p->nx, p->ny, p->dtype == PM_FP64, cus);
+    c->tile = pm::tile_plan(p->nx, p->ny, p->dtype == PM_FP64, c->pow, cus);
   if (const size_t off = pair ? lay.off_pair : lay.off_tile) {
     c->k32b = c->k32;
     c->k32b.f = (float*)((char*)dev_ws + off + lay.off_f);

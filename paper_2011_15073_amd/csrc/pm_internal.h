@@ -169,11 +169,12 @@ hipError_t launch_write_header(void* dst, int64_t steps, uint64_t tag, uint64_t 
 // launch, tile by tile, from the natural-layout state in src (even step count)
 // to dst (pm_tile.hip).  tile_plan: ts = 0 for a grid above the limits, where
 // one step per launch is as fast.
-constexpr int64_t TILE_NODES_F32 = 520 * 520, TILE_NODES_F64 = 264 * 264;
+constexpr int64_t TILE_NODES_F32 = 520 * 520, TILE_NODES_F64 = 360 * 360;
+constexpr size_t TILE_BYTES = size_t(32) << 20;  // largest second region (rows are padded: thin grids)
 struct TilePlan {
   int w, h, ts;  // region in nodes, most steps per launch
 };
-TilePlan tile_plan(int nx, int ny, bool fp64, int cus);
+TilePlan tile_plan(int nx, int ny, bool fp64, bool pow, int cus);
 template <typename T>
 hipError_t launch_tile(const KParams<T>& src, const KParams<T>& dst, const TilePlan& plan, int ts, hipStream_t s, bool pow,
                        bool logda);

@@ -145,7 +145,10 @@ constexpr int TILE_TOP_F32 = 1024, TILE_TOP_F64 = 768;  // largest regions (regi
 // step / this kernel: 460^2 6.7 / 6.1, 500^2 7.0 / 6.7, 510^2 7.0 / 7.2, 520^2
 // 7.9 / 7.4, 400 x 650 7.4 / 6.1, 650 x 400 7.5 / 7.5, 130 x 2000 8.1 / 7.4 (without
 // the rounds in the model the regions chosen took 6.4, 6.6, 7.6, 8.0, 6.2, 8.7, 9.0).
-TilePlan tile_plan(int nx, int ny, bool fp64, int cus) {
+// In FP64 the viscosity solve leaves room for two waves per SIMD: 280^2 6.6 /
+// 5.6, 255 x 333 6.8 / 5.7, 100 x 900 7.0 / 5.7, but with three 300^2 6.8 / 7.7;
+// n = 1: 264^2 4.5 / 3.3, 300^2 4.8 / 3.2, 340^2 5.4 / 4.0, 360^2 6.0 / 5.4, 400^2 6.6 / 7.8.
+TilePlan tile_plan(int nx, int ny, bool fp64, bool pow, int cus) {
   TilePlan best{0, 0, 0};
   if ((int64_t)nx * ny > (fp64 ? TILE_NODES_F64 : TILE_NODES_F32)) return best;
   const double F = fp64 ? 2.0 : 1.8, b = fp64 ? 0.6 : 0.55, c = fp64 ? 0.85 : 0.55, d = fp64 ? 1.4 : 0.53;
@@ -157,6 +160,7 @@ TilePlan tile_plan(int nx, int ny, bool fp64, int cus) {
       for (int ts = 2; ts <= 8 && 2 * ts < w && 2 * ts < h; ++ts) {
         const int64_t tiles = tiles_along(nx, w, ts) * tiles_along(ny, h, ts);
         const double waves = (double)((tiles + cus - 1) / cus) * (n / 64) / 4.0;
+        if (fp64 && pow && waves > 2.0) continue;
         const int fit = fp64 ? (n <= 256 ? 2 : 1) : (n <= 256 ? 5 : n <= 512 ? 3 : 1);  // workgroups on a CU at a time
         const int64_t rounds = (tiles + (int64_t)cus * fit - 1) / ((int64_t)cus * fit);
         const double us = (F + (double)(rounds - 1) * (F + 1.2) + b * waves) / ts + c + d * waves;

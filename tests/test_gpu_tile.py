@@ -18,7 +18,7 @@ BIG32 = [(384, 384), (520, 520)]
 
 
 @pytest.mark.parametrize("dtype,size", [(d, s) for s in SIZES for d in ("fp32", "fp64")] +
-                         [("fp64", (264, 264))] + [("fp32", s) for s in BIG32])
+                         [("fp64", s) for s in ((264, 264), (255, 333), (300, 300), (360, 360))] + [("fp32", s) for s in BIG32])
 @pytest.mark.parametrize("n,logda,rounding", [(1.0, False, "nearest"), (0.6, True, "nearest"), (0.8, False, "auto")])
 def test_tile_kernel_equals_single_steps(dtype, size, n, logda, rounding):
     nx, ny = size
