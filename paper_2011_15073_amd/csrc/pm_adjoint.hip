@@ -28,9 +28,10 @@ using namespace pm::dev;
 constexpr double LN2 = 0.693147180559945309417232121458176568;
 constexpr double LN10 = 2.302585092994045684017991454684364208;
 
-// sqrt(x) and 1 / sqrt(x) for x of ordinary size, to about an ulp: the hardware
-// estimate and Goldschmidt's iteration twice (10 instructions; the library's
-// square root and a division take 30).
+// sqrt(x) and 1 / sqrt(x), x >= 0, to about an ulp: the hardware estimate and
+// Goldschmidt's iteration twice (10 instructions; the library's square root and
+// a division take 30).  At x = 0 (a cell without porous resistance) the
+// iteration is 0 * inf: there the root is x, and its reciprocal the estimate.
 struct Root {
   double sqrt, rsqrt;
 };
@@ -44,7 +45,9 @@ __device__ __forceinline__ Root root(double x) {
   g = __builtin_fma(g, r, g);
   h = __builtin_fma(h, r, h);
   g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-  return Root{g, 2.0 * h};
+  constexpr int ZERO = 0x60;  // +0 and -0
+  const bool edge = __builtin_amdgcn_class(x, ZERO);
+  return Root{edge ? x : g, edge ? y : 2.0 * h};
 }
 
 // Viscosity of one node in FP64 with the data the adjoint needs.
