@@ -30,8 +30,9 @@ constexpr double LN10 = 2.302585092994045684017991454684364208;
 
 // sqrt(x) and 1 / sqrt(x), x >= 0, to about an ulp: the hardware estimate and
 // Goldschmidt's iteration twice (10 instructions; the library's square root and
-// a division take 30).  At x = 0 (a cell without porous resistance) the
-// iteration is 0 * inf: there the root is x, and its reciprocal the estimate.
+// a division take 30).  At x = 0 (a cell without porous resistance) and at
+// infinity (one whose resistance, squared, overflows) the iteration is 0 * inf:
+// there the root is x, and its reciprocal the estimate.
 struct Root {
   double sqrt, rsqrt;
 };
@@ -45,8 +46,8 @@ __device__ __forceinline__ Root root(double x) {
   g = __builtin_fma(g, r, g);
   h = __builtin_fma(h, r, h);
   g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
-  constexpr int ZERO = 0x60;  // +0 and -0
-  const bool edge = __builtin_amdgcn_class(x, ZERO);
+  constexpr int ZERO_OR_INF = 0x260;  // -0, +0 and +inf
+  const bool edge = __builtin_amdgcn_class(x, ZERO_OR_INF);
   return Root{edge ? x : g, edge ? y : 2.0 * h};
 }
 

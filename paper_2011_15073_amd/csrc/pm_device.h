@@ -33,8 +33,8 @@ __device__ __forceinline__ int band_of_block(int b, int G) {
 // Arithmetic helpers.  FP32 uses the hardware approximations directly
 // (v_rcp_f32, v_exp_f32, v_log_f32, v_sqrt_f32, about 1 ulp): the FP32 path is
 // held to 1e-4 against the FP64 oracle.  FP64 uses the library exp2 / log2 /
-// sqrt and correctly rounded reciprocals: frcp where the argument is of
-// ordinary size by construction, fdiv1 (IEEE division) where it may not be.
+// sqrt and rounded reciprocals: frcp where the argument cannot be subnormal,
+// fdiv1 (IEEE division) where it can.
 #ifndef PM_FAST_MATH
 #define PM_FAST_MATH 1
 #endif
@@ -53,19 +53,24 @@ template <> __device__ __forceinline__ float flog2<float>(float x) { return log2
 template <> __device__ __forceinline__ float fexp2<float>(float x) { return exp2f(x); }
 template <> __device__ __forceinline__ float fsqrt<float>(float x) { return sqrtf(x); }
 #endif
-// 1 / x for x of ordinary size (2^-1000 < |x| < 2^1000): the hardware estimate
-// and Newton's iteration r += r (1 - x r) three times, each residual exact by
-// FMA; the third makes it the correctly rounded quotient.  7 instructions
-// instead of the 11 of a division, whose other four scale extreme arguments:
-// with nine reciprocals per node update 1501 x 1031 FP64 54.5 -> 53.3 us per
-// step, the 27-case FP64 sweep 135.3 -> 134.4.  (The same for the square roots
-// needs a branch for zero velocities and was slower where one wave per SIMD
-// waits for it: 160^2 3.36 -> 3.44 us.)
+// 1 / x for every x but subnormal ones and those above 2^1000 (there to an ulp):
+// the hardware estimate and Newton's iteration r += r (1 - x r) three times, each
+// residual exact by FMA; from an estimate within an ulp the third gives the
+// correctly rounded quotient (Markstein's theorem; a significand of all ones, its
+// exception, may end an ulp off).  v_div_fixup puts in the quotients of 0 and of
+// infinity, which the iteration turns into NaN: a resistance whose square
+// overflows makes c0 + sqrt(..) infinite, and the node stands still.  8
+// instructions instead of the 11 of a division, whose other three scale extreme
+// arguments: with nine reciprocals per node update 1501 x 1031 FP64 takes 53.4 us
+// per step without the fixup, 53.7 with it, 54.6 with divisions.  (The same for
+// the square roots needs a branch for zero velocities and was slower where one
+// wave per SIMD waits for it: 160^2 3.36 -> 3.44 us.)
 template <> __device__ __forceinline__ double frcp<double>(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
   r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_amdgcn_div_fixup(r, x, 1.0);
 }
 template <typename T> __device__ __forceinline__ T fdiv1(T x) {  // 1 / x for any x (FP32: as frcp)
   if constexpr (std::is_same<T, double>::value) return 1.0 / x;

@@ -6,6 +6,7 @@ import torch
 
 import paper_2011_15073_amd as P
 from paper_2011_15073_amd import inputs
+from pairs import gpu_for, oracle_for
 from test_gpu_adjoint import torch_vjp
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +67,58 @@ def test_backward_with_clear_cells(T, C):
     # from rest, cells of equal resistance to rounding
     assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max()
     assert an == pytest.approx(bn, rel=1e-12) and aR == pytest.approx(bR, rel=1e-12)
+
+
+@pytest.mark.parametrize("n", [0.6, 1.0, 1.4])
+@pytest.mark.parametrize("step_kernel", ["auto", "single"])
+def test_solid_cells_match_the_oracle(n, step_kernel):
+    """Cells whose resistance, squared, is around or beyond the largest FP64 number
+    stand still: |u| < |v| / 1e153, and 0 beyond."""
+    nx, ny = 70, 19
+    ld, solid = plane(nx, ny, [-160.0, -200.0, -290.0])
+    kw = dict(n=n, Ra=1e4, **PHYS)
+    cav = gpu_for(nx, ny, logda=torch.from_numpy(ld), step_kernel=step_kernel, **kw)
+    orc = oracle_for(nx, ny, logda=ld, **kw)
+    f0, g0 = inputs.random_state(nx, ny, seed=7, amp=0.02, amp_T=0.1)
+    cav.set_populations(torch.from_numpy(f0), torch.from_numpy(g0))
+    orc.set_state(f0, g0)
+    for k in (1, 4):
+        cav.step(k)
+        orc.step(k)
+        for a, b in zip(cav.populations(), orc.state()):
+            assert np.abs(a.cpu().numpy() - b).max() <= 1e-13
+    U = np.abs(cav.fields()[0].cpu().numpy())
+    assert U[solid].max() <= 1e-150 and U[ld <= -200.0].max() == 0.0
+
+
+def test_solid_scalar_darcy_number_matches_the_oracle():
+    kw = dict(n=0.8, Da=1e-200, Ra=1e4, **PHYS)
+    cav, orc = gpu_for(20, **kw).step(7), oracle_for(20, **kw).step(7)
+    for a, b in zip(cav.populations(), orc.state()):
+        assert np.abs(a.cpu().numpy() - b).max() <= 1e-13
+
+
+@pytest.mark.parametrize("n", [0.7, 1.0, 1.4])
+def test_adjoint_step_with_solid_cells(n):
+    """Against a central difference of the oracle's step in a random direction.
+    On a plane without such cells the same difference is within 3e-10 |lambda| of
+    autograd's derivative (h = 1e-7: as much truncation as rounding)."""
+    nx, ny = 21, 13
+    ld, _ = plane(nx, ny, [-160.0, -200.0, -290.0])
+    rng = np.random.default_rng(5)
+    lam, d = rng.standard_normal((14, ny, nx)), rng.standard_normal((14, ny, nx))
+    f0, g0 = inputs.random_state(nx, ny, seed=7, amp=0.03, amp_T=0.2)
+    kw = dict(n=n, Ra=1e4, **PHYS)
+    cav = gpu_for(nx, ny, logda=torch.from_numpy(ld), **kw)
+    cav.set_populations(torch.from_numpy(f0), torch.from_numpy(g0))
+    lam_g, gld, gn, gRa = P.vjp_step(cav, torch.from_numpy(lam))
+    lam_g = lam_g.cpu().numpy()
+
+    def L(h):
+        orc = oracle_for(nx, ny, logda=ld, **kw)
+        orc.set_state(f0 + h * d[:9], g0 + h * d[9:])
+        return (lam * np.concatenate(orc.step(1).state())).sum()
+
+    fd = (L(1e-7) - L(-1e-7)) / 2e-7
+    assert (lam_g * d).sum() == pytest.approx(fd, abs=1e-8 * np.linalg.norm(lam_g))
+    assert np.isfinite(gld.cpu().numpy()).all() and np.isfinite([gn, gRa]).all()
