@@ -105,9 +105,12 @@ __device__ __forceinline__ NuSol nu_fp64(const AdjParams& a, double A, double B)
   double g2 = A + B * s * s;
   double L = log2(g2);
   for (int it = 0; it < 60; ++it) {
-    const double rg = 1.0 / g2;
+    // 1 / g2 overflows where g2 is subnormal (ahead of the front of a flow that
+    // sets in from rest the shear falls by a tenth of a decade per node)
+    const bool weak = g2 < 0x1p-1000;
+    const double rg = 1.0 / g2, x = 3.0 * a.nm1 * B * s * s * s * nu;
     const double G = (y - a.lc0) - hn * L;
-    const double dG = 1.0 + 3.0 * a.nm1 * B * s * s * s * nu * rg;
+    const double dG = 1.0 + (weak ? x / g2 : x * rg);
     double yn = y - G * frcp<double>(dG);
     if (!(g2 > 0.0)) yn = G < 0.0 ? a.y_hi : a.y_lo;
     yn = fmin(fmax(yn, a.y_lo), a.y_hi);
@@ -119,7 +122,7 @@ __device__ __forceinline__ NuSol nu_fp64(const AdjParams& a, double A, double B)
       s -= 3.0 * dnu * s * s;
       break;
     }
-    if (fabs(d) < 0x1p-13) {
+    if (fabs(d) < 0x1p-13 && !weak) {
       nu *= 1.0 + t * (1.0 + t * (0.5 + t * (1.0 / 6.0 + t * (1.0 / 24.0))));
       s = frcp<double>(3.0 * nu + 0.5);
       const double g2n = A + B * s * s, e = (g2n - g2) * rg;

@@ -122,3 +122,55 @@ def test_adjoint_step_with_solid_cells(n):
     fd = (L(1e-7) - L(-1e-7)) / 2e-7
     assert (lam_g * d).sum() == pytest.approx(fd, abs=1e-8 * np.linalg.norm(lam_g))
     assert np.isfinite(gld.cpu().numpy()).all() and np.isfinite([gn, gRa]).all()
+
+
+FORCES = [1e-152, 1e-153, 1e-154, 1e-155, 1e-156, 1e-157, 1e-158, 1e-160]
+
+
+@pytest.mark.parametrize("n", [0.6, 1.4])
+@pytest.mark.parametrize("step_kernel", ["auto", "single"])
+def test_viscosity_at_subnormal_shear(n, step_kernel):
+    """A cavity at rest but for a uniform force of 1e-152 .. 1e-160: away from the
+    heated walls the shear rate squared runs through the subnormal numbers, and
+    the viscosity is the oracle's, the bound that weak shear lands on (FP32
+    start of the FP64 solve: 2^-24 of log2 nu <= 10)."""
+    for gx in FORCES:
+        kw = dict(n=n, Da=1e-2, Ra=1e5, gx=gx, **PHYS)
+        cav = gpu_for(64, 24, step_kernel=step_kernel, **kw).step(6)
+        ref = oracle_for(64, 24, **kw).step(6).macros()["nu"][:, 8:56]
+        nu = cav.viscosity().cpu().numpy()[:, 8:56]
+        assert np.abs(nu / ref - 1).max() <= 1e-6, gx
+
+
+def forced(nx, ny, n, gx, steps):
+    """A cavity without body force in the state of one with the force gx after
+    `steps` steps from rest (the adjoint takes no body force): its saved state
+    behind the header of the other's, 256 bytes with the physics' hash."""
+    kw = dict(n=n, Da=1e-2, Ra=1e5, **PHYS)
+    cav = gpu_for(nx, ny, **kw).step(steps)
+    buf = cav.save_state()
+    buf[256:] = gpu_for(nx, ny, gx=gx, **kw).step(steps).save_state()[256:]
+    cav.load_state(buf)
+    return cav
+
+
+@pytest.mark.parametrize("n", [0.6, 1.0, 1.4])
+def test_adjoint_step_at_subnormal_shear(n):
+    """The same states: the adjoint step differs from that of the state without
+    the force by about the force's size, so not at all in FP64."""
+    lam = torch.from_numpy(1e3 * np.random.default_rng(2).standard_normal((14, 24, 64)))
+    out = [P.vjp_step(forced(64, 24, n, gx, 6), lam) for gx in [0.0] + FORCES]
+    for gx, (l, _, gn, gRa) in zip(FORCES, out[1:]):
+        assert np.isfinite(gn), gx
+        assert (l - out[0][0]).abs().max() <= 1e-12 * out[0][0].abs().max(), gx
+        assert gRa == pytest.approx(out[0][3], rel=1e-12), gx
+
+
+def test_adjoint_step_at_subnormal_shear_next_to_newtonian():
+    """n = 1 + 1e-9 has its root between the bounds at any shear: next to n = 1
+    (viscosity and gradients within 1e-9 times the 1000 octaves of the shear)."""
+    lam = torch.from_numpy(1e3 * np.random.default_rng(2).standard_normal((14, 4, 64)))
+    for gx in FORCES[1:5]:
+        a, b = (P.vjp_step(forced(64, 4, n, gx, 6), lam) for n in (1.0 + 1e-9, 1.0))
+        assert (a[0] - b[0]).abs().max() <= 1e-5 * b[0].abs().max(), gx
+        assert a[2] == pytest.approx(b[2], rel=1e-5) and a[3] == pytest.approx(b[3], rel=1e-5), gx
