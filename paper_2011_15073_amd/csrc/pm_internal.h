@@ -103,7 +103,7 @@ constexpr size_t NEAR_BYTES = size_t(256) << 20;
 #endif
 constexpr int TILE = PM_TILE;   // nodes per workgroup (one row segment)
 
-constexpr int MARCH_WAVES = 4;   // strips (waves) per workgroup of the multi-step pass
+constexpr int MARCH_WAVES = 4;   // most strips (waves) per workgroup of the multi-step pass
 constexpr int RED_BLOCKS = 1024; // partial-result slots of the Nusselt number and the residual
 constexpr int GRID_Y_MAX = 65535; // largest gridDim.y of any launch: taller grids loop over rows
 
@@ -183,7 +183,7 @@ hipError_t launch_tile(const KParams<T>& src, const KParams<T>& dst, const TileP
 // (pm_march.hip).  march_plan: ts = 0 where one step per pass is faster (not
 // with force); launch_march takes ts = 2, and in FP32 also 3.
 struct MarchPlan {
-  int ts, rows;  // most steps per pass, output rows per workgroup
+  int ts, rows, waves;  // most steps per pass; output rows and strips (waves) per workgroup
 };
 MarchPlan march_plan(int nx, int ny, bool fp64, bool pow, int cus, bool force);
 template <typename T>

@@ -170,10 +170,11 @@ __device__ __forceinline__ void pull(const KParams<T>& p, const Rows<T>& cp, int
   }
 }
 
-// One workgroup: MARCH_WAVES adjacent strips by `rows` output rows.
+// One workgroup: a wave for each of up to MARCH_WAVES adjacent strips, by `rows`
+// output rows.
 template <typename T, bool POW, bool LOGDA, bool SR, int TS>
 __global__ __launch_bounds__(64 * MARCH_WAVES, sizeof(T) == 8 ? 2 : (TS == 2 ? 4 : 3)) void k_march(
-    KParams<T> src, T* __restrict__ dst_f, T* __restrict__ dst_g, int strips, int rows) {
+    KParams<T> src, T* __restrict__ dst_f, T* __restrict__ dst_g, int strips, int waves, int rows) {
   // Workgroups (row group major, strips minor) are dealt to the 8 XCDs in blocks
   // of 8 adjacent ones, so that the columns two of them share are mostly fetched
   // into one L2, while all XCDs advance through the same rows.  The last
@@ -184,11 +185,11 @@ __global__ __launch_bounds__(64 * MARCH_WAVES, sizeof(T) == 8 ? 2 : (TS == 2 ? 4
     const int xcd = blk & 7, q = blk >> 3;
     blk = ((q / XCD_BLOCK) * 8 + xcd) * XCD_BLOCK + q % XCD_BLOCK;
   }
-  const int across = (strips + MARCH_WAVES - 1) / MARCH_WAVES;
+  const int across = (strips + waves - 1) / waves;
   const int sy = blk / across;
   // a wave past the last strip repeats it and stores nothing: all waves of the
   // workgroup run the same rows and reach every barrier
-  const int s0 = __builtin_amdgcn_readfirstlane((blk - sy * across) * MARCH_WAVES + ((int)threadIdx.x >> 6));
+  const int s0 = __builtin_amdgcn_readfirstlane((blk - sy * across) * waves + ((int)threadIdx.x >> 6));
   const int sx = min(s0, strips - 1);
   const int lane = threadIdx.x & 63;
   const int nx = src.nx, ny = src.ny;
@@ -295,25 +296,43 @@ int march_strips(int nx, int ts) { return nx <= 64 ? 1 : (nx - 64 + (64 - 2 * ts
 //            2400^2 100 / 79 .. 102, 2600^2 112 .. 118 / 92 .. 119, 4096^2 293 / 195 .. 205;
 //            FP64 2600^2 246 .. 260 / 209 .. 249, 3000^2 342 .. 357 / 291 .. 350,
 //            4096^2 607 .. 623 / 551 .. 578, 6000^2 1440 .. 1462 / 915 .. 1324
-// In the few hundred steps in which a flow from rest sets in, FP64 waves at n < 1
-// need the most Newton steps and this pass is the slower one (4096^2 n = 0.8 753
-// against 710, n = 0.6 931 against 809); a run of 3000 steps from rest is still
-// 8% faster with it.
-// Narrow grids leave the last workgroup's waves without strips.
+// A flow that sets in from rest is no exception (FP64 4096^2 n = 0.6, 4800 steps 619 /
+// 562, no window of 240 steps slower; 2900^2 315 / 296).
+// FP64 takes it from 12 strips (128 x 64062, n = 0.8: 326 / 363; 250 x 32800 330 / 329).
 //
-// Rows: a workgroup of R output rows collides ts R + ts (ts + 1) rows, and
-// MARCH_PER_CU of them (4 waves of 141 registers; FP64 250) fit a CU.  With r
-// rounds of workgroups the time goes as the rows times f(r), measured at
-// 4096^2, 3000^2 and 2048^2: one or two rounds end as whole ones, later ones
-// overlap.  (4096^2, R = 24 / 36 / 44 / 48 / 56 / 72: 202 / 200 / 204 / 193 /
-// 219 / 221 us.)
+// Waves: four adjacent strips to a workgroup, unless more than an eighth of the
+// waves had none then; apart from each other they take longer by `apart`.  FP32
+// 250 x 58000, 5 strips, us per step with 1 / 2 / 3 / 4 waves: n = 0.8 204 / 250 / 269
+// / 308, n = 1 177 / 182 / 193 / 215, one step per pass 304 and 310, the earlier
+// two-step kernel 220 and 211; 420 x 34523, 8 strips: 196 / 204 / 234 / 192 and 193 /
+// 175 / 172 / 148; FP64 1000 x 8200, 17 strips, n = 0.8: 293 / 334 / 379 / 339, one
+// step per pass 320.  (Wide grids: FP32 2700^2 n = 0.8 with 1 / 4 waves 103 / 90, FP64
+// 4096^2 n = 0.6 from rest 530 / 484.)
+//
+// Rows: a workgroup of R output rows collides ts R + ts (ts + 1) rows, and 12
+// waves (141 registers; FP64 8 of 250) fit a CU.  With r rounds of workgroups the
+// time goes as the rows times f(r), measured at 4096^2, 3000^2 and 2048^2: one or
+// two rounds end as whole ones, later ones overlap.  (4096^2, R = 24 / 36 / 44 / 48
+// / 56 / 72: 202 / 200 / 204 / 193 / 219 / 221 us.)
 MarchPlan march_plan(int nx, int ny, bool fp64, bool pow, int cus, bool force) {
-  MarchPlan best{0, 0};
+  MarchPlan best{0, 0, 0};
   const int ts = fp64 ? 2 : 3;
-  const int64_t strips = march_strips(nx, ts), across = (strips + MARCH_WAVES - 1) / MARCH_WAVES;
+  const int64_t strips = march_strips(nx, ts);
   const int64_t least = pow ? (fp64 ? 8000000 : 5500000) : (fp64 ? 1600000 : 1200000);
-  if (!force && ((int64_t)nx * ny < least || strips < 12)) return best;
-  const double slots = (fp64 ? 2.0 : 3.0) * cus;
+  if (!force && ((int64_t)nx * ny < least || (fp64 && strips < 12))) return best;
+  int waves = MARCH_WAVES;
+  const int64_t dealt = (strips + 3) / 4 * 4;
+  double least_cost = (double)dealt;
+  for (int w : {2, 3, 1}) {
+    const double apart = w == 3 ? (pow ? 1.08 : 1.3) : w == 2 ? (pow ? 1.06 : 1.15) : (pow ? 1.02 : 1.28);
+    const double cost = (double)((strips + w - 1) / w * w) * apart;
+    if ((dealt - strips) * 8 > dealt && cost < least_cost) {
+      least_cost = cost;
+      waves = w;
+    }
+  }
+  const int64_t across = (strips + waves - 1) / waves;
+  const double slots = (double)((fp64 ? 8 : 12) / waves) * cus;
   double best_cost = 1e300;
   for (int R = 16; R <= 56; ++R) {
     const double r = (double)(across * std::max(1, ny / R)) / slots;
@@ -321,7 +340,7 @@ MarchPlan march_plan(int nx, int ny, bool fp64, bool pow, int cus, bool force) {
     const double cost = (double)(ts * R + ts * (ts + 1)) * f;
     if (cost < best_cost) {
       best_cost = cost;
-      best = MarchPlan{ts, R};
+      best = MarchPlan{ts, R, waves};
     }
   }
   return best;
@@ -330,13 +349,13 @@ MarchPlan march_plan(int nx, int ny, bool fp64, bool pow, int cus, bool force) {
 template <typename T>
 hipError_t launch_march(const KParams<T>& src, const KParams<T>& dst, const MarchPlan& plan, int ts, hipStream_t s,
                         bool pow, bool logda) {
-  if (src.px || src.py || plan.rows < 1) return hipErrorInvalidValue;
+  if (src.px || src.py || plan.rows < 1 || plan.waves < 1 || plan.waves > MARCH_WAVES) return hipErrorInvalidValue;
   const int strips = march_strips(src.nx, ts);
-  const int64_t groups = (int64_t)((strips + MARCH_WAVES - 1) / MARCH_WAVES) * ((src.ny + plan.rows - 1) / plan.rows);
+  const int64_t groups = (int64_t)((strips + plan.waves - 1) / plan.waves) * ((src.ny + plan.rows - 1) / plan.rows);
   if (groups > 0x7fffffff) return hipErrorInvalidValue;
 #define PM_M(POW, LOG, SR, TS)                                                                                     \
-  hipLaunchKernelGGL((k_march<T, POW, LOG, SR, TS>), dim3((unsigned)groups), dim3(64 * MARCH_WAVES), 0, s, src, dst.f, \
-                     dst.g, strips, plan.rows)
+  hipLaunchKernelGGL((k_march<T, POW, LOG, SR, TS>), dim3((unsigned)groups), dim3(64 * plan.waves), 0, s, src, dst.f,  \
+                     dst.g, strips, plan.waves, plan.rows)
 #define PM_M_TS(POW, LOG, SR)                                   \
   do {                                                          \
     if (ts == 2) PM_M(POW, LOG, SR, 2);                         \
