@@ -34,8 +34,9 @@
  *     context, one private non-blocking stream on which pm_step captures its
  *     HIP graphs, those graphs, and 8 KB of pinned host memory for results,
  *     all released by pm_destroy (a sweep or an adjoint likewise releases
- *     what it creates in its own destroy call); up to 64 of the pinned blocks
- *     are kept for later contexts.
+ *     what it creates in its own destroy call); the pinned memory is taken
+ *     from slabs of 512 KB shared by the process's contexts, of which at most
+ *     one is kept without any in use.
  *   - A context is bound to the HIP stream given to pm_init; every call
  *     enqueues on that stream.  Calls that return host values (pm_nu,
  *     pm_residual, pm_run_to_steady) synchronise that stream.  A context is

@@ -271,44 +271,81 @@ namespace {
 
 // Pinned host memory that a kernel writes its RED_BLOCKS partial results to and
 // the host reads after the stream: no copy (which costs a kernel and a staging
-// buffer: pm_nu at 64^2 takes 17 us, 26 with the copy).  Freeing such memory waits for the whole device, so up to
-// HOST_SLOTS_KEPT blocks of destroyed contexts are kept for the next ones; every
-// use ends with a synchronisation of its stream, so a kept block has no writer.
-// Allocation is allowed while some stream is being captured.
-constexpr size_t HOST_SLOTS_KEPT = 64;
-std::mutex host_slots_mutex;
-double* host_slots_kept[HOST_SLOTS_KEPT];
-size_t host_slots_n = 0;
+// buffer: pm_nu at 64^2 takes 17 us, 26 with the copy).  An allocation takes 70 us
+// and freeing it waits for the whole device, 270 us, so contexts take blocks of
+// slabs of 64 (a sweep of 300 cases is created and destroyed in 130 .. 143 ms,
+// 200 .. 202 with allocations of their own for all but 64); a slab without blocks in
+// use is given back unless it is the only one.
+// Every use of a block ends with a synchronisation of its stream, so a free block
+// has no writer.  Allocation is allowed while some stream is being captured.
+struct HostSlab {
+  double* base;
+  uint64_t used;  // bit b: block b is some context's
+  HostSlab* next;
+};
+constexpr size_t HOST_BLOCK = pm::RED_BLOCKS, HOST_SLAB = 64 * HOST_BLOCK;  // doubles
+std::mutex host_slabs_mutex;
+HostSlab* host_slabs = nullptr;
 
-hipError_t host_slots_get(double** p) {
-  {
-    std::lock_guard<std::mutex> lock(host_slots_mutex);
-    if (host_slots_n) {
-      *p = host_slots_kept[--host_slots_n];
-      return hipSuccess;
-    }
-  }
+// op() with allocations allowed during other threads' and streams' captures.
+template <typename F>
+hipError_t capture_relaxed(F&& op) {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
   if (e != hipSuccess) return e;
-  e = hipHostMalloc((void**)p, pm::RED_BLOCKS * sizeof(double), hipHostMallocPortable);
-  if (e != hipSuccess) *p = nullptr;
-  const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
-  return e == hipSuccess ? back : e;
+  e = op();
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return e;
 }
 
-void host_slots_put(double* p) {
+// A free block of the slabs, or nullptr (the mutex is held).
+double* host_block_take() {
+  for (HostSlab* s = host_slabs; s; s = s->next)
+    if (~s->used) {
+      const int b = __builtin_ctzll(~s->used);
+      s->used |= uint64_t(1) << b;
+      return s->base + b * HOST_BLOCK;
+    }
+  return nullptr;
+}
+
+hipError_t host_block_get(double** p) {
   {
-    std::lock_guard<std::mutex> lock(host_slots_mutex);
-    if (host_slots_n < HOST_SLOTS_KEPT) {
-      host_slots_kept[host_slots_n++] = p;
-      return;
+    std::lock_guard<std::mutex> lock(host_slabs_mutex);
+    if ((*p = host_block_take())) return hipSuccess;
+  }
+  HostSlab* s = new (std::nothrow) HostSlab{nullptr, 0, nullptr};
+  if (!s) return hipErrorOutOfMemory;
+  const hipError_t e = capture_relaxed(
+      [&] { return hipHostMalloc((void**)&s->base, HOST_SLAB * sizeof(double), hipHostMallocPortable); });
+  if (e != hipSuccess) {
+    delete s;
+    return e;
+  }
+  std::lock_guard<std::mutex> lock(host_slabs_mutex);
+  s->next = host_slabs;
+  host_slabs = s;
+  *p = host_block_take();
+  return hipSuccess;
+}
+
+void host_block_put(double* p) {
+  HostSlab* idle = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(host_slabs_mutex);
+    HostSlab** own = &host_slabs;
+    while (!(p >= (*own)->base && p < (*own)->base + HOST_SLAB)) own = &(*own)->next;
+    (*own)->used &= ~(uint64_t(1) << ((p - (*own)->base) / HOST_BLOCK));
+    int idles = 0;
+    for (HostSlab* s = host_slabs; s; s = s->next) idles += !s->used;
+    if (!(*own)->used && idles > 1) {
+      idle = *own;
+      *own = idle->next;
     }
   }
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
-  (void)hipHostFree(p);
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!idle) return;
+  (void)capture_relaxed([&] { return hipHostFree(idle->base); });
+  delete idle;
 }
 
 }  // namespace
@@ -565,7 +602,7 @@ int init_ctx(const pm_params* p, void* dev_ws, size_t ws_bytes, void* hip_stream
     delete c;
     return PM_EDEVICE;
   }
-  e = host_slots_get(&c->host);
+  e = host_block_get(&c->host);
   if (e != hipSuccess) {
     set_global_err("pinned host memory: %s", hipGetErrorString(e));
     pm_destroy(c);
@@ -601,7 +638,7 @@ void pm_destroy(pm_ctx* c) {
   for (auto& g : c->graph)
     if (g) (void)hipGraphExecDestroy(g);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  if (c->host) host_slots_put(c->host);
+  if (c->host) host_block_put(c->host);
   delete c;
 }
 
