@@ -273,24 +273,28 @@ __device__ __forceinline__ T w5(int q) {
   return q == 0 ? T(1.0 / 3.0) : T(1.0 / 6.0);
 }
 
-// Bound by its traffic, one read and one write of the state.  Streaming stores
-// leave the state in the caches: 2048^2 FP32 98 -> 84 us at an odd step count,
-// 4096^2 344 -> 325.
-template <typename T, bool ODD, typename O, typename S>
+// Bound by its traffic, one read and one write of the state.  STREAM (each
+// wave's piece of a row is whole lines): streaming stores, which leave the state
+// in the caches (2048^2 FP32 at an odd step count 82 -> 72 us, 4096^2 332 -> 317);
+// a line that two waves write parts of would go to memory twice (2049 x 2047
+// 79 -> 136, 1500 x 1031 34 -> 42, 100 x 40000 88 -> 119).
+template <typename T, bool ODD, typename O, bool STREAM, typename S>
 __global__ __launch_bounds__(TILE) void k_get_pop(KParams<T, S> p, O* f, O* g) {
   const int i = blockIdx.x * TILE + threadIdx.x;
   if (i >= p.nx) return;
   const int64_t n = (int64_t)p.nx * p.ny;
+  auto put = [](O* a, double v) {
+    if constexpr (STREAM) __builtin_nontemporal_store((O)v, a);
+    else *a = (O)v;
+  };
   for (int j = blockIdx.y; j < p.ny; j += gridDim.y) {
     T df[9], dg[5];
     load_node<T, ODD>(p, i, j, df, dg);
     const int64_t k = (int64_t)j * p.nx + i;
 #pragma unroll
-    for (int q = 0; q < 9; ++q)
-      __builtin_nontemporal_store((O)((double)df[q] + (double)w9<T>(q)), &f[q * n + k]);
+    for (int q = 0; q < 9; ++q) put(&f[q * n + k], (double)df[q] + (double)w9<T>(q));
 #pragma unroll
-    for (int q = 0; q < 5; ++q)
-      __builtin_nontemporal_store((O)((double)dg[q] + (double)w5<T>(q) * (double)p.T_ref), &g[q * n + k]);
+    for (int q = 0; q < 5; ++q) put(&g[q * n + k], (double)dg[q] + (double)w5<T>(q) * (double)p.T_ref);
   }
 }
 
@@ -573,13 +577,16 @@ template <typename T, typename S>
 hipError_t launch_get_pop(const KParams<T, S>& p, const Launch& L, int parity, void* f, void* g,
                           int out_fp64) {
   dim3 grid(L.tiles_x, std::min(p.ny, GRID_Y_MAX)), block(TILE);
-  if (parity) {
-    if (out_fp64) hipLaunchKernelGGL((k_get_pop<T, true, double, S>), grid, block, 0, L.stream, p, (double*)f, (double*)g);
-    else hipLaunchKernelGGL((k_get_pop<T, true, float, S>), grid, block, 0, L.stream, p, (float*)f, (float*)g);
-  } else {
-    if (out_fp64) hipLaunchKernelGGL((k_get_pop<T, false, double, S>), grid, block, 0, L.stream, p, (double*)f, (double*)g);
-    else hipLaunchKernelGGL((k_get_pop<T, false, float, S>), grid, block, 0, L.stream, p, (float*)f, (float*)g);
-  }
+  const size_t line = 128;
+  const bool stream = (size_t)p.nx * (out_fp64 ? 8 : 4) % line == 0 && ((uintptr_t)f | (uintptr_t)g) % line == 0;
+#define PM_G(ODD, O, STREAM) \
+  hipLaunchKernelGGL((k_get_pop<T, ODD, O, STREAM, S>), grid, block, 0, L.stream, p, (O*)f, (O*)g)
+#define PM_G1(ODD, O) do { if (stream) PM_G(ODD, O, true); else PM_G(ODD, O, false); } while (0)
+#define PM_G2(ODD) do { if (out_fp64) PM_G1(ODD, double); else PM_G1(ODD, float); } while (0)
+  if (parity) PM_G2(true); else PM_G2(false);
+#undef PM_G2
+#undef PM_G1
+#undef PM_G
   return hipGetLastError();
 }
 
