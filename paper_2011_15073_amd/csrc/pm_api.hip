@@ -400,7 +400,10 @@ hipError_t dispatch(pm_ctx* c, F&& fn) {
 // whole groups of 2 ts steps from an even step count run as two passes, region
 // A -> B -> A, so that the state always ends in its own region, the last group
 // with the ts that is left; the remaining steps use the single-step kernel in
-// place.
+// place.  Passes of one step pay off only where a row fills less than half a wave
+// of the single-step kernel (a call of two steps, two such passes / two single
+// steps: 3 x 9000 FP32 22 / 32 us, 20^2 17.4 / 18.7, 64^2 FP64 21.5 / 20.0, 256^2 26.9 /
+// 23.6); the multi-step pass takes at least two.
 hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_steps) {
   pm::Launch L = c->launch;
   L.stream = s;
@@ -416,7 +419,7 @@ hipError_t enqueue_steps(pm_ctx* c, hipStream_t s, int64_t k, int64_t start_step
   hipError_t e = hipSuccess;
   int64_t t = 0;
   if (const int most = c->march.ts ? c->march.ts : c->tile.ts) {
-    const int least = c->march.ts ? 2 : 1;
+    const int least = !c->march.ts && c->p.nx < 32 ? 1 : 2;
     if ((start_steps & 1) && k > 0) e = single(t++);
     while (e == hipSuccess && k - t >= 2 * least) {
       const int ts = (int)std::min<int64_t>(most, (k - t) / 2);
