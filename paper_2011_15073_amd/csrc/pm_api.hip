@@ -70,7 +70,8 @@ int step_width_for(int nx, int ny, int dtype) {
 
 // Large cavities take several steps per pass (pm::launch_march) between two
 // population regions, when a second one of at most 64 GiB (FP64: 32) covers
-// them; ny up to PAIR_NY_MAX.  The plan for the size is made with 256 CUs, so
+// them; ny up to PAIR_NY_MAX, which is part of the interface (pm_march.hip's grid
+// would take more).  The plan for the size is made with 256 CUs, so
 // that the workspace does not depend on the device; PM_STEP_PAIR asks for the
 // pass on any FP32 cavity.
 constexpr int PAIR_NY_MAX = 24 * 65535;
@@ -965,10 +966,13 @@ int sweep_fail(pm_sweep* s, int code, const char* fmt, ...) {
 // Only the tiles of live cases are scheduled, so cases that have stopped cost
 // no workgroups (the step kernel still checks the live flag).  The cases are
 // independent between two stopping tests: where their states do not fit the
-// last-level cache together they take a chunk's steps in groups that do (27 FP64
-// cases, 370 MB: 126 us per step in one group, 120.5 in two of 185 MB; in groups
-// of half that 129, of a quarter 140: a group has to fill the chip).  Interleaved
-// tiles stay one group.
+// last-level cache together they take a chunk's steps in groups of about equal
+// size (27 FP64 cases, 370 MB: 126 us per step in one group, 120.5 in two of 185
+// MB; in groups of half that 129, of a quarter 140: a group has to fill the chip,
+// so none is split off for what goes beyond the cache).  A group may exceed the
+// cache by part of its last case, 200 + 100 of 200, 100, 110 and 100 MB, and a case
+// above it is a group of its own: those run as streaming ones.  Interleaved tiles
+// stay one group.
 void build_schedule(pm_sweep* s) {
   const int n = s->ncases;
   auto live = [&](int i) { return s->h_live.empty() || s->h_live[i] != 0; };

@@ -23,10 +23,11 @@
 // is worth more than anything else here: 256^2 FP32 2.7 us per step in bands,
 // 4.1 in launch order.
 //
-// us per step, one step per launch / this kernel: FP32 64^2 3.25 / 1.59, 128^2
-// 3.35 / 1.80, 256^2 3.80 / 2.69, 384^2 5.31 / 3.72, 512^2 7.12 / 6.46 (640^2
-// 9.7 / 9.5: the overlap's share grows, one step per launch from there on);
-// FP64 64^2 4.29 / 2.58, 160^2 4.72 / 3.26, 256^2 5.33 / 4.86 (320^2 7.2 / 7.1).
+// us per step at n = 0.8, one step per launch / this kernel: FP32 64^2 3.25 / 1.59,
+// 128^2 3.35 / 1.80, 256^2 3.80 / 2.69, 384^2 5.31 / 3.72, 512^2 7.12 / 6.46 (640^2
+// 9.7 / 9.5: the overlap's share grows; tile_plan ends at 520^2); FP64 64^2 4.29 /
+// 2.58, 160^2 4.72 / 3.26, 256^2 5.33 / 4.86 (320^2 7.2 / 7.1: there n != 1 takes one
+// step per launch, n = 1 this kernel up to 360^2).
 // The time is launch + memory latency (about 2.5 us) and the steps' own chains
 // (1.1 us each with one wave per SIMD, 2.6 with four; FP64 2.3 with one).
 #include "pm_device.h"
@@ -137,8 +138,10 @@ constexpr int TILE_TOP_F32 = 1024, TILE_TOP_F64 = 768;  // largest regions (regi
 // The region and step count with the shortest modelled time per step, for the
 // grids on which this kernel is the faster one.  With W waves of 64 threads on
 // each SIMD of the fullest CU a launch takes F + b W + ts (c + d W) us; the
-// constants are fitted to 48^2 .. 512^2 in FP32 (F 1.8, b 0.55, c 0.55, d 0.53;
-// within 10%) and 48^2 .. 256^2 in FP64 (2.0, 0.6, 0.85, 1.4).  A workgroup of
+// constants are fitted, at n = 0.8, to 48^2 .. 512^2 in FP32 (F 1.8, b 0.55, c 0.55, d
+// 0.53; within 10%) and 48^2 .. 256^2 in FP64 (2.0, 0.6, 0.85, 1.4).  n = 1 uses the
+// same plan, though its chain c + d W is shorter (FP64 64^2 1.3 us, modelled 2.7):
+// nothing is fitted there but the limits below.  A workgroup of
 // more than 512 threads (FP64: 256) has a CU to itself, and each further round of
 // them starts with its loads exposed.  Near the FP32 limit the plan is compared
 // with one step per launch, 2.9 us + 16.2 ps per node.  n = 0.8, us per step, one
